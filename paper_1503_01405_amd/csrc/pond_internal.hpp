@@ -70,6 +70,7 @@ struct K2Args {
     const void* hchirp;     // packed float16, kRowChirp: split middle pass chirp
     const double* geo;      // kRowInv: [n2][n1] turns per unit DM of each bin (shared by the trials)
     double dm;              // kRowInv: the trial's DM (chirp exp(-2 pi i frac(dm geo)))
+    int32_t chain;          // kRowInv: blocks per workgroup (set by launch_k2)
 };
 
 // Split middle pass, for rows longer than one workgroup's LDS holds (n1 =

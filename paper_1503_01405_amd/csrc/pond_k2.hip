@@ -4,6 +4,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -62,10 +63,10 @@ __global__ void __launch_bounds__(256) k2_build_table(void* __restrict__ tab, in
 //                  (float16: 61 -> 92, occupancy 8 -> 5 waves) and time.
 //   MODE kRowFwd:  twiddle and forward FFT only, in place: leaves the block's
 //                  spectrum, row k2 holding bins k2 + n2 k1 (float2 twiddle table).
-//   MODE kRowInv:  spectrum (in) times one trial's chirp, inverse FFT,
-//                  conjugate twiddle, to `out`; the chirp is formed from the
-//                  trial's DM and the shared float64 table of turns per unit
-//                  DM (dm_chirp).
+//   MODE kRowInv:  a kernel of its own (k2_row_inv): spectrum (in) times one
+//                  trial's chirp, inverse FFT, conjugate twiddle, to `out`; the
+//                  chirp is formed from the trial's DM and the shared float64
+//                  table of turns per unit DM (dm_chirp).
 //   MODE kRowInvPlain: kRowInv without the chirp (float32 arithmetic only).
 //   MODE kRowChirp: forward FFT, chirp (float2 or float16 table in the rows'
 //                  order), inverse FFT, in place, no twiddles (the sub-rows
@@ -159,7 +160,7 @@ k2_row(K2Args a) {
     const uint32_t toff = (uint32_t)(min(r, n2 - 1 - row0) << LOG2N1) + (uint32_t)j;
     const int64_t rowbase = (((int64_t)b << a.log2n2) + row0) << LOG2N1;
     T* rows = reinterpret_cast<T*>(a.work) + rowbase;
-    constexpr bool INV = MODE == kRowInv || MODE == kRowInvPlain;
+    constexpr bool INV = MODE == kRowInvPlain;
     const T* src = INV ? reinterpret_cast<const T*>(a.in) + rowbase : rows;
     T* dst = INV ? reinterpret_cast<T*>(a.out) + rowbase : rows;
 
@@ -172,7 +173,6 @@ k2_row(K2Args a) {
         const uint2* tab = reinterpret_cast<const uint2*>(a.htable) + ((int64_t)row0 << LOG2N1);
         const h2* tw4 = reinterpret_cast<const h2*>(a.htw4) + ((int64_t)row0 << LOG2N1);
         const h2* chirp = reinterpret_cast<const h2*>(a.hchirp) + ((int64_t)row0 << LOG2N1);
-        const double* geo = a.geo + ((int64_t)row0 << LOG2N1);
         // Element u + i of the workgroup's rows through buffer descriptors:
         // u (uniform) is the scalar offset, i the lane's, so that a thread's
         // 16 accesses share one vector offset per array.
@@ -195,8 +195,7 @@ k2_row(K2Args a) {
             const int u = MX ? 16 * (e >> 2) + (e & 3) * TPV : TPV * e;
             const uint32_t i = MX ? mxo : to;
             const h2 x = buf_ld<h2>(rsrc, i * (uint32_t)sizeof(T), u * (int)sizeof(T));
-            if constexpr (MODE == kRowInv) v[e] = cmul(x, to_h2(dm_chirp(a.dm, *at(geo + u, i * 8u))));
-            else if constexpr (MODE == kRowChirp) v[e] = x;
+            if constexpr (MODE == kRowChirp) v[e] = x;
             else v[e] = cmul(x, tw_at(u, i));
         }
         // kRowFull: the chirp of each element is fetched during the forward
@@ -214,11 +213,11 @@ k2_row(K2Args a) {
             // first LDS use of the row: no barrier before the first stores
             if constexpr (MODE == kRowFull || MODE == kRowChirp)
                 fft_mx<LOG2N1, -1, true, false, false>(v, j, lrow.base, ttab, fetch_chirp);
-            else if constexpr (MODE != kRowInv) fft_mx<LOG2N1, -1, true, false, false>(v, j, lrow.base, ttab);
+            else fft_mx<LOG2N1, -1, true, false, false>(v, j, lrow.base, ttab);
         } else {
             if constexpr (MODE == kRowFull || MODE == kRowChirp)
                 fft_wg<LOG2N1, -1, true, 1>(v, j, tb, lrow, ttab, fetch_chirp);
-            else if constexpr (MODE != kRowInv) fft_wg<LOG2N1, -1, true, 1>(v, j, tb, lrow, ttab);
+            else fft_wg<LOG2N1, -1, true, 1>(v, j, tb, lrow, ttab);
         }
         if constexpr (MODE == kRowFwd) {
             constexpr float osc = 1.0f / (float)(1 << Sched<LOG2N1>::kHalfRem);
@@ -252,10 +251,8 @@ k2_row(K2Args a) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) wo[e] = tw_at(TPV * e, t2);
         };
-        if constexpr (MX && MODE == kRowFull)  // input in registers (canonical), moved through LDS
+        if constexpr (MX)  // input in registers (canonical), moved through LDS
             fft_mx<LOG2N1, +1, false, false, true, true>(v, j, lrow.base, ttab, fetch_tw);
-        else if constexpr (MX)  // kRowInv: input loaded in the matrix-core layout, first LDS use
-            fft_mx<LOG2N1, +1, false, false, false>(v, j, lrow.base, ttab, fetch_tw);
         else fft_wg<LOG2N1, +1, false, 1>(v, j, tb, lrow, ttab, fetch_tw);
         asm volatile("" ::: "memory");
         to = opaque(toff);
@@ -287,7 +284,6 @@ k2_row(K2Args a) {
         };
         const float2* tw4 = a.tw4 + ((int64_t)row0 << LOG2N1);
         const float2* chirp = a.chirp + ((int64_t)row0 << LOG2N1);
-        const double* geo = a.geo + ((int64_t)row0 << LOG2N1);
         float2 v[16];
         uint32_t to = opaque(toff);
 #pragma unroll
@@ -297,8 +293,6 @@ k2_row(K2Args a) {
                 v[e] = cmul(x, tw_row(TPV * e, to));
             } else if constexpr (MODE == kRowFwd) {
                 v[e] = cmul(x, *at(tw4 + TPV * e, to * 8u));
-            } else if constexpr (MODE == kRowInv) {
-                v[e] = cmul(x, dm_chirp(a.dm, *at(geo + TPV * e, to * 8u)));
             } else {
                 v[e] = x;  // kRowInvPlain: the filter was applied before (real input path); kRowChirp
             }
@@ -324,7 +318,7 @@ k2_row(K2Args a) {
             fft_wg<LOG2N1, -1>(v, j, tb, lrow, nullptr, fetch_chirp);
 #pragma unroll
             for (int e = 0; e < 16; ++e) v[e] = cmul(v[e], ch[e]);
-        } else if constexpr (MODE != kRowInv && MODE != kRowInvPlain) {
+        } else if constexpr (MODE != kRowInvPlain) {
             fft_wg<LOG2N1, -1>(v, j, tb, lrow);
         }
         if constexpr (MODE == kRowFwd) {
@@ -367,6 +361,135 @@ k2_row(K2Args a) {
             for (int e = 0; e < 16; ++e)
                 Elem<T>::store(at(dst + TPV * e, to * (uint32_t)sizeof(T)), cscale(cmulc(v[e], wo[e]), a.scale));
         }
+    }
+}
+
+// The trials' inverse rows (MODE kRowInv): one workgroup takes its row (ROWS
+// rows for short rows) in `chain` consecutive blocks.  The chirp of a bin
+// depends on the trial and the bin only, so it is formed once per
+// workgroup and kept in registers for all of its blocks: forming it for each
+// block was half of the kernel's VALU work (83 instructions per element,
+// which kept the VALU busy 90% of the time).  In the float16 forms the next
+// block's spectrum is read while this one is transformed (16 registers more;
+// without it the search takes 1.5% longer, and 11% with the registers capped
+// for six waves per SIMD).  Packed float16, 2^23, 8 blocks per launch: 156 ->
+// 129 us, 4.2 TB/s of rows read and written (a large copy: 5.4); the search
+// of 128 trials over 10 s 167.7 -> 149.9 ms, its 2^23 group in float32 137 ->
+// 125 ms.
+// Float32 arithmetic with a last stage of radix 8 or 16 has no registers to
+// keep the chirp in (up to 18 spilled of 128): one block per workgroup there.
+template <int LOG2N1, bool F16>
+constexpr bool kInvChain = F16 || LOG2N1 % 4 == 1 || LOG2N1 % 4 == 2;
+template <int LOG2N1, class T, bool F16, bool MXF>
+__global__ void __launch_bounds__(K2Shape<LOG2N1>::THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+k2_row_inv(K2Args a) {
+    using Sh = K2Shape<LOG2N1>;
+    using V = std::conditional_t<F16, h2, float2>;
+    constexpr bool MX = F16 && MXF && kMxShape<LOG2N1, false>;
+    constexpr bool kChain = kInvChain<LOG2N1, F16>;
+    constexpr int TPV = Sh::TPV;
+    __shared__ V lds[Sh::ROWS * Sh::STRIDE];
+    __shared__ __align__(16) h2 ttab[F16 ? TwTab<LOG2N1>::kSize : 1];
+
+    const int logical = xcd_logical(blockIdx.x, gridDim.x);
+    const int n2 = 1 << a.log2n2;
+    const int row_groups = (n2 + Sh::ROWS - 1) / Sh::ROWS;
+    const int nchains = (a.nblocks + a.chain - 1) / a.chain;
+    if (logical >= row_groups * nchains) return;
+    const int rg = logical / nchains;
+    const int bfirst = (logical - rg * nchains) * a.chain;
+    const int bend = kChain ? min(a.nblocks, bfirst + a.chain) : bfirst + 1;
+
+    const int r = threadIdx.x / TPV;
+    const int j = threadIdx.x - r * TPV;
+    const bool valid = rg * Sh::ROWS + r < n2;
+    using RowL = std::conditional_t<F16 && !MX && LOG2N1 >= 12, StageRowLds<V>, PadLds<V>>;
+    const RowL lrow{lds + r * Sh::STRIDE};
+
+    StageBases<LOG2N1, V> tb;
+    tb.load(j, a.tw1);
+    const int row0 = min(rg * Sh::ROWS, n2 - 1);
+    const uint32_t toff = (uint32_t)(min(r, n2 - 1 - row0) << LOG2N1) + (uint32_t)j;
+    const uint32_t ioff = MX ? toff - (uint32_t)j + (uint32_t)mx_pos<false, TPV>(j, 0) : toff;
+    constexpr uint32_t kEl = (uint32_t)Sh::ROWS << LOG2N1;  // elements of the rows
+    const int64_t row_at = (int64_t)row0 << LOG2N1;
+    const double* geo = a.geo + row_at;
+    const int64_t bstep = (int64_t)1 << (LOG2N1 + a.log2n2);
+    const T* src = reinterpret_cast<const T*>(a.in) + (int64_t)bfirst * bstep + row_at;
+    T* dst = reinterpret_cast<T*>(a.out) + (int64_t)bfirst * bstep + row_at;
+    if constexpr (F16) {
+        if (threadIdx.x < 64) fill_twiddle_tables<LOG2N1, 64, !MX>(ttab, a.tw1, threadIdx.x);
+    }
+    // element of the workgroup's rows held at register e on input
+    auto in_u = [](int e) { return MX ? 16 * (e >> 2) + (e & 3) * TPV : TPV * e; };
+    auto load = [&](const T* from, V(&x)[16]) {
+        if constexpr (F16) {
+            const BufRes rb = buf_res(uniform_ptr(from), kEl * (uint32_t)sizeof(T));
+            const uint32_t i = opaque(ioff);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = buf_ld<h2>(rb, i * (uint32_t)sizeof(T), in_u(e) * (int)sizeof(T));
+        } else {
+            const uint32_t i = opaque(ioff);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = Elem<T>::load(at(from + TPV * e, i * (uint32_t)sizeof(T)));
+        }
+    };
+    auto chirp = [&](int e) {
+        const float2 c = dm_chirp(a.dm, *at(geo + in_u(e), opaque(ioff) * 8u));
+        if constexpr (F16) return to_h2(c);
+        else return c;
+    };
+    V ch[16], x[16];
+    if constexpr (kChain) {
+        load(src, x);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) ch[e] = chirp(e);
+    }
+    V wo[16];
+    auto fetch_tw = [&] {
+        const uint32_t t2 = opaque(toff);
+        if constexpr (F16) {
+            const BufRes rb = buf_res(reinterpret_cast<const h2*>(a.htw4) + row_at, kEl * 4u);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) wo[e] = buf_ld<h2>(rb, t2 * 4u, TPV * e * 4);
+        } else {
+            const float2* tw4 = a.tw4 + row_at;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) wo[e] = *at(tw4 + TPV * e, t2 * 8u);
+        }
+    };
+    constexpr bool kPf = F16;
+    for (int b = bfirst; b < bend; ++b) {
+        V v[16];
+        if constexpr (kChain) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = cmul(x[e], ch[e]);
+        } else {
+            const uint32_t i = opaque(ioff);
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                v[e] = cmul(Elem<T>::load(at(src + TPV * e, i * (uint32_t)sizeof(T))), chirp(e));
+        }
+        src += bstep;
+        if (kPf && b + 1 < bend) load(src, x);
+        if constexpr (MX) fft_mx<LOG2N1, +1, false, false, true>(v, j, lrow.base, ttab, fetch_tw);
+        else if constexpr (F16) fft_wg<LOG2N1, +1, false, 1>(v, j, tb, lrow, ttab, fetch_tw);
+        else fft_wg<LOG2N1, +1>(v, j, tb, lrow, nullptr, fetch_tw);
+        if (valid) {
+            const uint32_t to = opaque(toff);
+            if constexpr (F16) {
+                const BufRes rb = buf_res(uniform_ptr(dst), kEl * (uint32_t)sizeof(T));
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    buf_st<h2>(rb, to * (uint32_t)sizeof(T), TPV * e * (int)sizeof(T), cmulc(v[e], wo[e]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    Elem<T>::store(at(dst + TPV * e, to * (uint32_t)sizeof(T)), cscale(cmulc(v[e], wo[e]), a.scale));
+            }
+        }
+        dst += bstep;
+        if (kChain && !kPf && b + 1 < bend) load(src, x);
     }
 }
 
@@ -466,6 +589,39 @@ static hipError_t k2_one(const K2Args& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Blocks per workgroup of the trials' inverse rows: as many as leave
+// kInvGroups workgroups in the launch, four per CU (the search of 128 trials
+// in packed float16: 150.2 ms; 2,048 workgroups 152.9, 512 152.0).
+constexpr int kInvGroups = 1024;
+template <class T, bool F16, bool MX, int LOG2N1>
+static hipError_t k2_inv_one(const K2Args& a, hipStream_t s) {
+    using Sh = K2Shape<LOG2N1>;
+    const int row_groups = ((1 << a.log2n2) + Sh::ROWS - 1) / Sh::ROWS;
+    const int want = (kInvGroups + row_groups - 1) / row_groups;  // chains per row
+    K2Args c = a;
+    c.chain = kInvChain<LOG2N1, F16> ? std::max(1, a.nblocks / want) : 1;
+    const int grid = (row_groups * ((a.nblocks + c.chain - 1) / c.chain) + 7) & ~7;
+    hipLaunchKernelGGL((k2_row_inv<LOG2N1, T, F16, MX>), dim3(grid), dim3(Sh::THREADS), 0, s, c);
+    return hipGetLastError();
+}
+
+template <class T, bool F16, bool MX = false>
+static hipError_t k2_inv_dispatch(int log2n1, const K2Args& a, hipStream_t s) {
+    switch (log2n1) {
+        case 5: return k2_inv_one<T, F16, MX, 5>(a, s);
+        case 6: return k2_inv_one<T, F16, MX, 6>(a, s);
+        case 7: return k2_inv_one<T, F16, MX, 7>(a, s);
+        case 8: return k2_inv_one<T, F16, MX, 8>(a, s);
+        case 9: return k2_inv_one<T, F16, MX, 9>(a, s);
+        case 10: return k2_inv_one<T, F16, MX, 10>(a, s);
+        case 11: return k2_inv_one<T, F16, MX, 11>(a, s);
+        case 12: return k2_inv_one<T, F16, MX, 12>(a, s);
+        case 13: return k2_inv_one<T, F16, MX, 13>(a, s);
+        case 14: return k2_inv_one<T, F16, MX, 14>(a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 template <class T, int MODE, bool F16, bool MX = false>
 static hipError_t k2_dispatch(int log2n1, const K2Args& a, hipStream_t s) {
     switch (log2n1) {
@@ -498,7 +654,15 @@ hipError_t launch_k2(int prec, int mode, int log2n1, const K2Args& a, hipStream_
     switch (mode) {
         case kRowFull: return k2_prec<kRowFull>(prec, log2n1, a, s);
         case kRowFwd: return k2_prec<kRowFwd>(prec, log2n1, a, s);
-        case kRowInv: return k2_prec<kRowInv>(prec, log2n1, a, s);
+        case kRowInv:
+            // the search's forms
+            switch (prec) {
+                case kFp32: return k2_inv_dispatch<float2, false>(log2n1, a, s);
+                case kHalf: return k2_inv_dispatch<__half2, true>(log2n1, a, s);
+                case kMixed: return k2_inv_dispatch<__half2, true, true>(log2n1, a, s);
+                case kMixedValu: return k2_inv_dispatch<__half2, false>(log2n1, a, s);
+                default: return hipErrorInvalidValue;
+            }
         case kRowChirp:
             // sub-rows of the split middle pass only
             if (log2n1 != kSplitLog2M1) return hipErrorInvalidValue;
