@@ -81,13 +81,14 @@ struct pond_plan {
     // elements, the filter and fold in real samples.
     int32_t kind = POND_INPUT_COMPLEX;
     int bpe = 2;                // input bytes per element
-    // Rows up to 2^13: one fused middle pass (k2_real_pair) with rtab =
-    // (four-step twiddle, filter) and wk; longer rows: forward rows, split,
-    // inverse rows with tw4 and rtab = (split twiddle, filter).
-    bool real_fused = false;
+    // Tables of its middle pass (RealPairArgs), n2/2 + 1 rows of n1 each; or,
+    // float16 storage with rows of 2^14, three passes (real_three): tw4 for
+    // all rows and rtab = (split twiddle, filter).
+    bool real_three = false;
     float2* tw4 = nullptr;
+    float4* real_ad = nullptr;
+    float2* real_b = nullptr;
     float4* rtab = nullptr;     // [nfft + 1]
-    float2* wk = nullptr;       // [n2 + n1]
 
     void* work = nullptr;
     int8_t* tail[2] = {nullptr, nullptr};
@@ -199,7 +200,7 @@ void free_plan_memory(pond_plan* p) {
     for (hipEvent_t e : p->event_pool) (void)hipEventDestroy(e);
     p->event_pool.clear();
     void* ptrs[] = {p->work,   p->tail[0], p->tail[1], p->tw1,     p->tw2,         p->table,
-                    p->htable, p->tw4,     p->rtab,    p->wk,      p->tw_n1,       p->tw_hi,
+                    p->htable, p->tw4,     p->real_ad, p->real_b, p->rtab, p->tw_n1,       p->tw_hi,
                     p->tw_lo,  p->acc_sum, p->acc_cnt, p->part_sum, p->part_cnt, p->status, p->chirp_split};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -546,11 +547,11 @@ namespace {
 // Builds the filter table of the plan's middle pass (for the taper alpha).
 hipError_t build_filter(pond_plan* p, double alpha) {
     const int lsb = p->kind == POND_INPUT_REAL_LSB ? 1 : 0;
-    if (p->kind != POND_INPUT_COMPLEX && p->real_fused)
-        return launch_real_build_pair_table(p->rtab, p->wk, p->log2n1, p->log2n2, p->chirp_a, p->f0, p->bw, lsb,
-                                            alpha, nullptr);
-    if (p->kind != POND_INPUT_COMPLEX)
+    if (p->kind != POND_INPUT_COMPLEX && p->real_three)
         return launch_real_build_table(p->rtab, p->log2n1, p->log2n2, p->chirp_a, p->f0, p->bw, lsb, alpha, nullptr);
+    if (p->kind != POND_INPUT_COMPLEX)
+        return launch_real_build_pair_table(p->tw4, p->real_ad, p->real_b, p->log2n1, p->log2n2, p->chirp_a, p->f0,
+                                            p->bw, lsb, alpha, nullptr);
     if (p->log2m2 > 0)
         return launch_build_split_chirp(p->chirp_split, f16_arith(p->precision), p->log2n1, p->log2n2, p->chirp_a,
                                         p->f0, p->df, alpha, nullptr);
@@ -647,14 +648,16 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
         if (e == hipSuccess) chk(launch_partial_twiddles(p->tw_lo, nlo, nfft, nullptr));
     }
     if (kind != POND_INPUT_COMPLEX) {
-        p->real_fused = p->log2n1 <= kRealPairMaxLog2N1;
-        chk(hipMalloc(reinterpret_cast<void**>(&p->rtab), (size_t)(nfft + 1) * sizeof(float4)));
-        if (p->real_fused) {
-            chk(hipMalloc(reinterpret_cast<void**>(&p->wk), (size_t)(n1 + n2) * sizeof(float2)));
-        } else {
-            chk(hipMalloc(reinterpret_cast<void**>(&p->tw4), (size_t)nfft * sizeof(float2)));
+        p->real_three = precision == POND_MIXED_VALU && p->log2n1 == kMaxLog2RowN1;
+        const size_t entries = (size_t)(p->real_three ? n2 : n2 / 2 + 1) * (size_t)n1;
+        chk(hipMalloc(reinterpret_cast<void**>(&p->tw4), entries * sizeof(float2)));
+        if (p->real_three) {
+            chk(hipMalloc(reinterpret_cast<void**>(&p->rtab), (size_t)(nfft + 1) * sizeof(float4)));
             if (e == hipSuccess)
                 chk(launch_k2_build_split_tables(p->tw4, nullptr, p->log2n1, p->log2n2, 0.0, p->f0, p->df, nullptr));
+        } else {
+            chk(hipMalloc(reinterpret_cast<void**>(&p->real_ad), entries * sizeof(float4)));
+            chk(hipMalloc(reinterpret_cast<void**>(&p->real_b), entries * sizeof(float2)));
         }
     } else if (p->log2m2) {
         // chirp_split, above
@@ -1018,7 +1021,6 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     // normalised (1/n2), the row pass scales by 1/n1, the inverse column
     // pass by 1, so every stored intermediate stays within the input range.
     const float k1_scale = std::ldexp(1.0f, -n2log);
-    const float k2_scale = std::ldexp(1.0f, -p->log2n1);
     const float k3_scale = 1.0f;
 
     int64_t b = p->blocks_done;
@@ -1058,33 +1060,26 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
         });
         if (e != hipSuccess) return fail(e);
 
-        K2Args a2{};
-        a2.work = p->work;
-        a2.nblocks = (int32_t)nb;
-        a2.log2n2 = n2log;
-        a2.tw1 = p->tw1;
-        a2.table = p->table;
-        a2.htable = p->htable;
-        a2.scale = k2_scale;
-        if (real && p->real_fused) {
-            RealPairArgs rp{p->work, (int32_t)nb, n2log, p->tw1, p->rtab, p->wk, k2_scale};
-            e = timed(1, nb, [&] { return launch_real_pair(p->precision, p->log2n1, rp, stream); });
-        } else if (real) {
-            // Forward rows, the real split with the filter (in place), then
-            // the inverse rows with no further filter: one timed middle pass.
+        if (real && p->real_three) {
+            K2Args a2{};
+            a2.work = p->work;
+            a2.nblocks = (int32_t)nb;
+            a2.log2n2 = n2log;
+            a2.tw1 = p->tw1;
             a2.tw4 = p->tw4;
-            a2.in = p->work;
-            a2.out = p->work;
-            a2.chirp = nullptr;
+            a2.scale = std::ldexp(1.0f, -p->log2n1);
             RealSplitArgs rs{p->work, (int32_t)nb, p->log2n1, n2log, p->rtab};
             e = timed(1, nb, [&] {
                 hipError_t r = launch_k2(p->precision, kRowFwd, p->log2n1, a2, stream);
-                if (r == hipSuccess) r = launch_real_split(p->precision, rs, stream);
+                if (r == hipSuccess) r = launch_real_split(rs, stream);
                 K2Args ai = a2;
                 ai.scale = 1.0f;
                 if (r == hipSuccess) r = launch_k2(p->precision, kRowInvPlain, p->log2n1, ai, stream);
                 return r;
             });
+        } else if (real) {
+            RealPairArgs rp{p->work, (int32_t)nb, n2log, p->tw1, p->tw4, p->real_ad, p->real_b};
+            e = timed(1, nb, [&] { return launch_real_pair(p->precision, p->log2n1, rp, stream); });
         } else {
             e = timed(1, nb, [&] { return run_middle(p, p->work, (int)nb, stream); });
         }

@@ -44,8 +44,8 @@ struct K1Args {
 
 // K2: four-step twiddle, forward row FFT (length n1), chirp, inverse row
 // FFT, conjugate twiddle.
-// kRowInvPlain: kRowInv with no filter (float32 arithmetic forms; the real
-// input path's longest rows, filtered by real_split before).
+// kRowInvPlain: kRowInv with no filter, in place (float16 storage with float32
+// arithmetic, rows of 2^14: the real input path, filtered by real_split before).
 // kRowChirp: forward row FFT, chirp, inverse row FFT, no twiddles (the
 // sub-rows of the split middle pass, rows of 2^kSplitLog2M1; chirp table in
 // their order).
@@ -131,8 +131,20 @@ struct K3Args {
     uint32_t* status;
 };
 
-// Real input path: split of the packed spectrum into the real transform's
-// bins, filter, recombination (see real_split).
+// Real input path: the middle pass over row pairs (see k2_real_pair).
+struct RealPairArgs {
+    void* data;             // [nblocks][n2][n1], forward column pass output, replaced in place
+    int32_t nblocks;
+    int32_t log2n2;
+    const float2* tw1;      // exp(-2 pi i t / n1), t < n1
+    const float2* tw4;      // [n2/2 + 1][n1] four-step twiddle
+    const float4* ad;       // [n2/2 + 1][n1] coefficients a and d of the bin
+    const float2* b;        // [n2/2 + 1][n1] coefficient b
+};
+hipError_t launch_real_pair(int prec, int log2n1, const RealPairArgs& a, hipStream_t s);
+hipError_t launch_real_build_pair_table(float2* tw4, float4* ad, float2* b, int log2n1, int log2n2, double chirp_a,
+                                        double f0, double bw, int lsb, double taper, hipStream_t s);
+// Float16 storage, rows of 2^14: split of the stored spectrum (see real_split).
 struct RealSplitArgs {
     void* data;             // [nblocks][n2][n1] spectrum of the packed block (/N), replaced in place
                             // by the spectrum of the filtered packed block
@@ -140,25 +152,11 @@ struct RealSplitArgs {
     int32_t log2n1, log2n2;
     const float4* tab;      // [N + 1] (W^k, M[k]) of the bin at each position, then bin N
 };
-// Real input path, fused middle pass (rows up to 2^13; see k2_real_pair).
-struct RealPairArgs {
-    void* data;             // [nblocks][n2][n1], forward column pass output, replaced in place
-    int32_t nblocks;
-    int32_t log2n2;
-    const float2* tw1;      // exp(-2 pi i t / n1), t < n1
-    const float4* tab;      // [N + 1] (four-step twiddle, M[k]) per block position; tab[N].z = M[N]
-    const float2* wk;       // [n2 + n1] exp(-i pi k2 / N), then exp(-i pi k1 / n1)
-    float scale;            // power-of-two scale of the forward row output
-};
-constexpr int kRealPairMaxLog2N1 = 13;
-hipError_t launch_real_pair(int prec, int log2n1, const RealPairArgs& a, hipStream_t s);
-hipError_t launch_real_build_pair_table(float4* tab, float2* wk, int log2n1, int log2n2, double chirp_a, double f0,
-                                        double bw, int lsb, double taper, hipStream_t s);
-hipError_t launch_k1_aip(int prec, int log2n2, const K1Args& a, hipStream_t s);
-hipError_t launch_real_split(int prec, const RealSplitArgs& a, hipStream_t s);
-hipError_t launch_k3_real(int prec, int log2n2, const K3Args& a, int grid, size_t dyn, hipStream_t s);
+hipError_t launch_real_split(const RealSplitArgs& a, hipStream_t s);
 hipError_t launch_real_build_table(float4* tab, int log2n1, int log2n2, double chirp_a, double f0, double bw,
                                    int lsb, double taper, hipStream_t s);
+hipError_t launch_k1_aip(int prec, int log2n2, const K1Args& a, hipStream_t s);
+hipError_t launch_k3_real(int prec, int log2n2, const K3Args& a, int grid, size_t dyn, hipStream_t s);
 
 // Incoherent (AID) mode: filterbank, then channel shift-and-sum and fold.
 struct AidArgs {

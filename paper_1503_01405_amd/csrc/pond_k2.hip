@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(256) k2_build_table(void* __restrict__ tab, in
 //                  trial's chirp, inverse FFT, conjugate twiddle, to `out`; the
 //                  chirp is formed from the trial's DM and the shared float64
 //                  table of turns per unit DM (dm_chirp).
-//   MODE kRowInvPlain: kRowInv without the chirp (float32 arithmetic only).
+//   MODE kRowInvPlain: inverse FFT and conjugate twiddle only, in place.
 //   MODE kRowChirp: forward FFT, chirp (float2 or float16 table in the rows'
 //                  order), inverse FFT, in place, no twiddles (the sub-rows
 //                  of the split middle pass; the float16 forms' input already
@@ -160,9 +160,8 @@ k2_row(K2Args a) {
     const uint32_t toff = (uint32_t)(min(r, n2 - 1 - row0) << LOG2N1) + (uint32_t)j;
     const int64_t rowbase = (((int64_t)b << a.log2n2) + row0) << LOG2N1;
     T* rows = reinterpret_cast<T*>(a.work) + rowbase;
-    constexpr bool INV = MODE == kRowInvPlain;
-    const T* src = INV ? reinterpret_cast<const T*>(a.in) + rowbase : rows;
-    T* dst = INV ? reinterpret_cast<T*>(a.out) + rowbase : rows;
+    const T* src = rows;
+    T* dst = rows;
 
     if constexpr (F16) {
         __shared__ __align__(16) h2 ttab[TwTab<LOG2N1>::kSize];
@@ -674,9 +673,8 @@ hipError_t launch_k2(int prec, int mode, int log2n1, const K2Args& a, hipStream_
                 default: return k2_one<__half2, kRowChirp, false, false, kSplitLog2M1>(a, s);
             }
         case kRowInvPlain:
-            // float32 arithmetic forms only (the real input path)
-            if (prec == kFp32) return k2_dispatch<float2, kRowInvPlain, false>(log2n1, a, s);
-            if (prec == kMixedValu) return k2_dispatch<__half2, kRowInvPlain, false>(log2n1, a, s);
+            if (prec == kMixedValu && log2n1 == kMaxLog2RowN1)
+                return k2_one<__half2, kRowInvPlain, false, false, kMaxLog2RowN1>(a, s);
             return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
