@@ -99,12 +99,12 @@ struct pond_plan {
     void* table = nullptr;      // float32 arithmetic forms: chirp (float32 storage) or twiddle and chirp
     void* htable = nullptr;     // float16 arithmetic forms: twiddle / 16 and chirp (8 bytes per entry)
     // Split middle pass (rows n1 = m2 2^13 longer than 2^14): tw1 then holds
-    // the sub-row twiddles, tw_n1 the row's, tw_hi / tw_lo the two-level
+    // the sub-row twiddles, tw_ck the row's (SplitColArgs), tw_hi / tw_lo the two-level
     // block twiddle, chirp_split the chirp in sub-row order (float2, or
     // float16 pairs for the float16 arithmetic forms).
     int log2m2 = 0;             // 0: rows transformed whole
     int log2s = 0;
-    float2* tw_n1 = nullptr;
+    float2* tw_ck = nullptr;
     float2* tw_hi = nullptr;
     float2* tw_lo = nullptr;
     void* chirp_split = nullptr;
@@ -200,7 +200,7 @@ void free_plan_memory(pond_plan* p) {
     for (hipEvent_t e : p->event_pool) (void)hipEventDestroy(e);
     p->event_pool.clear();
     void* ptrs[] = {p->work,   p->tail[0], p->tail[1], p->tw1,     p->tw2,         p->table,
-                    p->htable, p->tw4,     p->real_ad, p->real_b, p->rtab, p->tw_n1,       p->tw_hi,
+                    p->htable, p->tw4,     p->real_ad, p->real_b, p->rtab, p->tw_ck,       p->tw_hi,
                     p->tw_lo,  p->acc_sum, p->acc_cnt, p->part_sum, p->part_cnt, p->status, p->chirp_split};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -227,7 +227,7 @@ hipError_t run_middle(const pond_plan* p, void* work, int nb, hipStream_t stream
         return launch_k2(p->precision, kRowFull, p->log2n1, a2, stream);
     }
     const bool h = f16_arith(p->precision);
-    SplitColArgs sc{work, nb, p->log2n1, p->log2n2, p->tw_n1, p->tw_hi, p->tw_lo, p->log2s, 1.0f};
+    SplitColArgs sc{work, nb, p->log2n1, p->log2n2, p->tw_ck, p->tw_hi, p->tw_lo, p->log2s, 1.0f};
     sc.scale = std::ldexp(1.0f, -p->log2m2 - (h ? 4 : 0));
     hipError_t e = launch_split_cols(p->precision, false, sc, stream);
     if (e != hipSuccess) return e;
@@ -639,11 +639,11 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     if (p->log2m2) {
         p->log2s = (log2n + 1) / 2;
         const int64_t nlo = (int64_t)1 << p->log2s, nhi = nfft >> p->log2s;
-        chk(hipMalloc(reinterpret_cast<void**>(&p->tw_n1), (size_t)n1 * sizeof(float2)));
+        chk(hipMalloc(reinterpret_cast<void**>(&p->tw_ck), (size_t)n1 * sizeof(float2)));
         chk(hipMalloc(reinterpret_cast<void**>(&p->tw_hi), (size_t)nhi * sizeof(float2)));
         chk(hipMalloc(reinterpret_cast<void**>(&p->tw_lo), (size_t)nlo * sizeof(float2)));
         chk(hipMalloc(&p->chirp_split, (size_t)nfft * (f16_arith(precision) ? 4 : 8)));
-        if (e == hipSuccess) chk(launch_stage_twiddles(p->tw_n1, n1, nullptr));
+        if (e == hipSuccess) chk(launch_build_split_twiddles(p->tw_ck, p->log2n1, nullptr));
         if (e == hipSuccess) chk(launch_stage_twiddles(p->tw_hi, nhi, nullptr));
         if (e == hipSuccess) chk(launch_partial_twiddles(p->tw_lo, nlo, nfft, nullptr));
     }

@@ -85,13 +85,14 @@ struct SplitColArgs {
     void* work;             // [nblocks][n2][n1], in place
     int32_t nblocks;
     int32_t log2n1, log2n2;
-    const float2* tw_n1;    // exp(-2 pi i t / n1), t < n1
+    const float2* tw_ck;    // [k][c] exp(-2 pi i c k / n1), k < m2, c < m1
     const float2* tw_hi;    // exp(-2 pi i t 2^log2s / N), t < N / 2^log2s
     const float2* tw_lo;    // exp(-2 pi i t / N), t < 2^log2s
     int32_t log2s;
     float scale;            // applied to every output
 };
 hipError_t launch_split_cols(int prec, bool inverse, const SplitColArgs& a, hipStream_t s);
+hipError_t launch_build_split_twiddles(float2* tw, int log2n1, hipStream_t s);  // tw_ck
 // Chirp tables of the split middle pass, in sub-row order: entry (k2 m2 + k)
 // m1 + c' holds the inverse ISM response at frequency k2 + n2 (k + m2 c').
 // Float32 (float2) or packed float16 (times 2^-half_row_rem(kSplitLog2M1)).
