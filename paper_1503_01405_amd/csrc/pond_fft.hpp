@@ -149,6 +149,33 @@ struct DftConst<h2> {
     static constexpr float c8 = kC8h, s8 = kS8h;
 };
 
+// The values of two adjacent columns: the packed-float16 column passes'
+// 32-column tiles, one twiddle for both (8 bytes per access).
+struct __align__(8) hh2 {
+    h2 a, b;
+};
+__device__ __forceinline__ hh2 cadd(hh2 x, hh2 y) { return {cadd(x.a, y.a), cadd(x.b, y.b)}; }
+__device__ __forceinline__ hh2 csub(hh2 x, hh2 y) { return {csub(x.a, y.a), csub(x.b, y.b)}; }
+__device__ __forceinline__ hh2 cneg(hh2 x) { return {cneg(x.a), cneg(x.b)}; }
+__device__ __forceinline__ hh2 cscale(hh2 x, _Float16 s) { return {cscale(x.a, s), cscale(x.b, s)}; }
+__device__ __forceinline__ hh2 cmul(hh2 x, h2 w) { return {cmul(x.a, w), cmul(x.b, w)}; }
+__device__ __forceinline__ hh2 cmulc(hh2 x, h2 w) { return {cmulc(x.a, w), cmulc(x.b, w)}; }
+template <int DIR>
+__device__ __forceinline__ hh2 mul_i(hh2 x) { return {mul_i<DIR>(x.a), mul_i<DIR>(x.b)}; }
+template <int DIR>
+__device__ __forceinline__ hh2 mul_w8(hh2 x) { return {mul_w8<DIR>(x.a), mul_w8<DIR>(x.b)}; }
+template <int DIR>
+__device__ __forceinline__ hh2 mul_w8_3(hh2 x) { return {mul_w8_3<DIR>(x.a), mul_w8_3<DIR>(x.b)}; }
+template <int DIR>
+__device__ __forceinline__ hh2 mul_cs(hh2 x, float c, float s) { return {mul_cs<DIR>(x.a, c, s), mul_cs<DIR>(x.b, c, s)}; }
+template <>
+struct DftConst<hh2> : DftConst<h2> {};
+// Packed-float16 arithmetic, and the type of its twiddles.
+template <class V>
+constexpr bool kIsHalf = std::is_same<V, h2>::value || std::is_same<V, hh2>::value;
+template <class V>
+using TwiddleOf = std::conditional_t<kIsHalf<V>, h2, V>;
+
 // --------------------------------------------------------- small DFTs
 // In-place DFT of R values, natural order in and out:
 //   V[s] = sum_q v[q] exp(DIR * 2 pi i q s / R)   (DIR = -1 forward)
@@ -336,6 +363,8 @@ struct StageBases {
 // The packed-float16 transforms use the float32 stage bases.
 template <int LOG2L>
 struct StageBases<LOG2L, h2> : StageBases<LOG2L, float2> {};
+template <int LOG2L>
+struct StageBases<LOG2L, hh2> : StageBases<LOG2L, float2> {};
 
 // LDS layouts of a transform's vector (the position of an element is its
 // index in the vector).  put<D>(p0, x) / get<D>(p0) access position p0 + D
@@ -357,6 +386,31 @@ struct ColLds {
             return base + idx((uint32_t)p0) + kSlots(D);
         } else {
             return base + idx((uint32_t)(p0 + D));
+        }
+    }
+    template <int D, bool AL = false>
+    __device__ __forceinline__ void put(int p0, V x) const { *addr<D, AL>(p0) = x; }
+    template <int D>
+    __device__ __forceinline__ V get(int p0) const { return *addr<D>(p0); }
+};
+// The same tile without spare slots (K3): position p of a column at p ^ ((p /
+// 16) mod 4), so that the first stage's stores (16 positions apart in the
+// four column groups of a wave) fall in different banks too, and the tile is
+// a power of two.  Positions differ in their low two bits only, so an access
+// at p0 + D is one of four bases plus an immediate.
+template <class V>
+struct ColSwz {
+    V* base;
+    template <int D, bool AL = false>
+    __device__ __forceinline__ V* addr(int p0) const {
+        const uint32_t u = (uint32_t)p0;
+        if constexpr (AL && D < 16) {  // p0 a multiple of 16
+            return base + u * 16 + (((D & 3) ^ ((u >> 4) & 3)) << 4) + (D >> 2) * 64;
+        } else if constexpr (D % 64 == 0) {
+            return base + (u ^ ((u >> 4) & 3)) * 16 + D * 16;
+        } else {
+            const uint32_t w = u + D;
+            return base + (w ^ ((w >> 4) & 3)) * 16;
         }
     }
     template <int D, bool AL = false>
@@ -468,22 +522,22 @@ __device__ __forceinline__ void stage_tw_h(float2 base, h2 (&t)[16]) {
 // output q to position (jp - k) R + k + q NS.  With SCALE_IN the inputs
 // are first multiplied by 1/16 (float16 forward transforms).
 template <int L, int R, int NS, int DIR, bool LAST, bool SCALE_IN = false, class V, class Lds>
-__device__ __forceinline__ void stockham_stage(V (&v)[16], int j, V base, const Lds& st,
+__device__ __forceinline__ void stockham_stage(V (&v)[16], int j, TwiddleOf<V> base, const Lds& st,
                                                const h2* htw = nullptr) {
     // htw (float16 only): the stage's 16 twiddles of this thread (stage_tw_h).
-    constexpr bool HALF = std::is_same<V, h2>::value;
+    constexpr bool HALF = kIsHalf<V>;
     // Opaque to the optimiser: the twiddle powers and LDS addresses of a
     // stage are recomputed at each use instead of being shared between the
     // forward and inverse transforms (or hoisted out of loops) and held in
     // registers, which costs occupancy.
-    if constexpr (std::is_same<V, h2>::value) {
+    if constexpr (HALF) {
         asm volatile("" : "+v"(base), "+v"(j));
     } else {
         asm volatile("" : "+v"(base.x), "+v"(base.y), "+v"(j));
     }
     constexpr int BF = 16 / R;
     constexpr int TPV = L / 16;
-    V pw[R];
+    TwiddleOf<V> pw[R];
     if constexpr (NS > 1 && R == 16) {
         if constexpr (HALF) {
 #pragma unroll
@@ -509,7 +563,7 @@ __device__ __forceinline__ void stockham_stage(V (&v)[16], int j, V base, const 
 #pragma unroll
                     for (int q = 0; q < R; ++q) pw[q] = htw[u * R + q];
                 } else {
-                    const V bu = mul_w16<u>(base);
+                    const TwiddleOf<V> bu = mul_w16<u>(base);
                     powers<R>(bu, pw);
                 }
             }
@@ -716,17 +770,17 @@ __device__ __forceinline__ void fft_wg(V (&v)[16], int j, const StageBases<LOG2L
     using S = Sched<LOG2L>;
     constexpr int L = 1 << LOG2L;
     constexpr int TPV = L / 16;
-    constexpr bool HALF = std::is_same<V, h2>::value;
+    constexpr bool HALF = kIsHalf<V>;
     static_for<S::kStages>([&](auto si) {
         constexpr int s = decltype(si)::value;
         constexpr int R = S::radix(s);
         constexpr int NS = S::ns(s);
         constexpr bool LAST = (s == S::kStages - 1);
         constexpr bool SC = HALF_NORM && s > 0 && (s % 2 == 0);
-        V base;
+        TwiddleOf<V> base;
         h2 tw[16];
         if constexpr (HALF) {
-            base = cone<V>();
+            base = cone<h2>();
             if constexpr (NS > 1 && (TW == 2 || (TW == 1 && s == 1))) {
                 stage_tw_tab<LOG2L, s>(ttab, j, tw);
             } else if constexpr (NS > 1) {
