@@ -87,8 +87,9 @@ __device__ __forceinline__ BufRes buf_res(const void* base, uint32_t bytes) {
 }
 template <class V>
 __device__ __forceinline__ V buf_ld(const BufRes& b, uint32_t voff, int soff) {
-    static_assert(sizeof(V) == 4, "32-bit values");
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)voff, soff, 0));
+    static_assert(sizeof(V) == 4 || sizeof(V) == 8, "32 or 64-bit values");
+    if constexpr (sizeof(V) == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)voff, soff, 0));
+    else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(b.r, (int)voff, soff, 0));
 }
 template <class V>
 __device__ __forceinline__ void buf_st(const BufRes& b, uint32_t voff, int soff, V v) {
@@ -169,22 +170,20 @@ __device__ __forceinline__ double taper_w(double f, double bw, double alpha) {
     return 0.5 * (1.0 + cos(M_PI * fmin(af - flat, edge) / edge));
 }
 // ------------------------------------------------------------------- K3
-// Static LDS.  Float32 arithmetic: one float2 tile of 16 columns, reused for
-// the detected powers.  Packed float16: the padded float16 tile, a power
-// buffer of its own (16 floats per row) and the twiddle tables, so
-// that an item's powers are written without a barrier after the transform
-// and the next item's transform starts without one before its first
-// exchange.
+// Static LDS: the tile of 16 columns (float2, or float16 pairs and the twiddle
+// tables).
 template <int LOG2N2>
 struct K3Shape {
     static constexpr int L = 1 << LOG2N2;
     static constexpr int TPV = L / 16;
     static constexpr int THREADS = L;
     static constexpr size_t LDS = sizeof(float2) * 16 * L;
-    static constexpr size_t kHalfTile = ColLds<h2, true>::kSlots(L) * sizeof(h2);
-    static constexpr size_t kHalfPf = 16 * L * sizeof(float);
-    static constexpr size_t LDS_HALF = kHalfTile + kHalfPf + ((TwTab<LOG2N2>::kSize + 3) & ~3) * sizeof(h2);
-    static constexpr size_t lds(int form) { return form == kFormF16 || form == kFormMfma ? LDS_HALF : LDS; }
+    static constexpr size_t kHalfTile = sizeof(h2) * 16 * L;
+    static constexpr size_t LDS_HALF = kHalfTile + ((TwTab<LOG2N2>::kSize + 3) & ~3) * sizeof(h2);
+    static constexpr size_t LDS_WIDE = LDS_HALF + kHalfTile;  // tiles of 32 columns
+    static constexpr size_t lds(int form, bool wide = false) {
+        return form == kFormF16 || form == kFormMfma ? (wide ? LDS_WIDE : LDS_HALF) : LDS;
+    }
 };
 
 // Fold phase of output m (float64, as specified): x = (m + n_front) * inv_pfs,
@@ -206,22 +205,5 @@ __device__ __forceinline__ int64_t subint_rel(int64_t d, int64_t S, double inv_s
     if (r < 0) --k;
     else if (r >= S) ++k;
     return k;
-}
-
-// Add `val` (a power or a sum of `cnt` powers) to histogram entry `key`.
-__device__ __forceinline__ void fold_add(const K3Args& a, uint64_t* hsum, uint32_t* hcnt, int64_t sub_rel, int bin,
-                                         float val, uint32_t cnt, uint32_t& flags) {
-    const double dv = (double)val * kFoldScale;
-    if (!(dv < kFoldRangeLimit * kFoldScale)) flags |= 2u;
-    const uint64_t fx = isfinite(val) ? (uint64_t)__double2ull_rn(dv) : 0ull;
-    if (a.global_mode) {
-        const int64_t gk = (sub_rel + a.s_base - a.acc_s0) * a.nbins + bin;
-        atomicAdd((unsigned long long*)&a.acc_sum[gk], (unsigned long long)fx);
-        atomicAdd((unsigned long long*)&a.acc_cnt[gk], (unsigned long long)cnt);
-    } else {
-        const int key = (int)sub_rel * a.nbins + bin;
-        atomicAdd((unsigned long long*)&hsum[key], (unsigned long long)fx);
-        atomicAdd(&hcnt[key], cnt);
-    }
 }
 }  // namespace pond

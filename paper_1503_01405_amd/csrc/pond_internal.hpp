@@ -130,6 +130,12 @@ struct K3Args {
     uint64_t* acc_cnt;
     int64_t acc_s0;         // sub-integration held by accumulator slot 0
     uint32_t* status;
+    // set by launch_k3 / launch_k3_real
+    double nbins_d;         // nbins
+    double fold_safe0;      // bins from a group's first sample to its last, and
+    double fold_safe1;      // per turn of phase, what rounding can add to that
+    double samples_per_bin;
+    double inv_subint;      // 1 / subint
 };
 
 // Real input path: the middle pass over row pairs (see k2_real_pair).

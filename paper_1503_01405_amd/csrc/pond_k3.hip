@@ -10,12 +10,50 @@
 
 namespace pond {
 
-// Power buffer of the packed-float16 K3: row-major, 16 floats per row, the
-// four float4 quarters of a row rotated by (row / 4) mod 4, so that the
-// epilogue's float4 reads of 16 consecutive rows (one per lane) and the
-// detection's writes of four rows per wave use every bank once.
-__device__ __forceinline__ int k3h_pidx(int row, int col) {
+// Power buffer: row-major, 16 floats per row, the four float4 quarters of a
+// row rotated by (row / 4) mod 4, so that the epilogue's float4 reads of 16
+// consecutive rows (one per lane) and the detection's writes of four rows per
+// wave use every bank once.
+__device__ __forceinline__ int k3_pidx(int row, int col) {
     return row * 16 + ((((col >> 2) + (row >> 2)) & 3) << 2) + (col & 3);
+}
+// The same with 32 floats per row, rotated by 4 (row mod 8) floats.
+__device__ __forceinline__ int k3_pidx32(int row, int x) { return row * 32 + ((x + 4 * (row & 7)) & 31); }
+
+// A power in fixed point: round(val 2^16) to nearest even, 0 for a value that
+// is not finite (the product is exact in float32, and so are its two halves).
+__device__ __forceinline__ uint64_t fold_fixed(float val) {
+    float x = rintf(val * 65536.0f);
+    x = fabsf(x) < 18446744073709551616.0f ? x : 0.0f;
+    const float hi = floorf(x * 2.3283064365386963e-10f);
+    const float lo = fmaf(hi, -4294967296.0f, x);
+    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+}
+
+// The kernel's own arguments where the launch left them.  The epilogue of an
+// item reads what it needs from there, through a pointer the compiler cannot
+// see through: kept over the transform, its 40 or so scalars would be spilled
+// into vector registers.
+using K3Kernarg = const __attribute__((address_space(4))) K3Args;
+__device__ __forceinline__ K3Kernarg& k3_kernarg() {
+    K3Kernarg* p = (K3Kernarg*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *p;
+}
+
+// Add fx, the fixed-point sum of `cnt` powers, to the histogram: entry `bin` of
+// sub-integration s_base + sub_rel.
+__device__ __forceinline__ void k3_fold_add(K3Kernarg& a, uint64_t* hsum, uint32_t* hcnt, int sub_rel, int bin,
+                                            uint64_t fx, uint32_t cnt) {
+    if (a.global_mode) {
+        const int64_t gk = ((int64_t)sub_rel + a.s_base - a.acc_s0) * a.nbins + bin;
+        atomicAdd((unsigned long long*)&a.acc_sum[gk], (unsigned long long)fx);
+        atomicAdd((unsigned long long*)&a.acc_cnt[gk], (unsigned long long)cnt);
+    } else {
+        const int key = sub_rel * a.nbins + bin;
+        atomicAdd((unsigned long long*)&hsum[key], (unsigned long long)fx);
+        atomicAdd(&hcnt[key], cnt);
+    }
 }
 
 // REAL (real input path, float32 arithmetic): element m of the output is
@@ -24,37 +62,55 @@ __device__ __forceinline__ int k3h_pidx(int row, int col) {
 // (sums over decim elements = 2 decim real samples) is unchanged, and the
 // fold takes real sample r = 2 m + j with phase (r + 2 n_front) inv_pfs
 // (inv_pfs of the real sample rate).
-template <int LOG2N2, class T, int FORM, bool REAL = false>
-__global__ void __launch_bounds__(1 << LOG2N2) k3_colinv_detect_fold(K3Args a) {
+//
+// An item is 16 columns of a block: thread (c, j) transforms column c, holding
+// rows j + TPV e, and leaves the detected powers in LDS, in the tile the
+// transform has left; thread q then takes the 16 consecutive outputs of row q.
+// Bound: the exchanges' barriers and the strided tile reads in turn (2^23,
+// packed float16, per block: 14.4 us; 13.8 without the transform, 10.6 with
+// every tile in L2, 12.2 without the series, whose 4-byte stores fall in one
+// cache line each).  So the powers take no LDS of their own (68 KB instead of
+// 133) and the epilogue's scalars and float64 constants no registers (k3_kernarg,
+// K3Args), which lets two workgroups share a CU in packed float16 (TWO) and
+// float32 fetch its next tile; the fold phase of a group is one float64 product
+// and the second one only near a bin's edge.  2^23, per block in launches of 4 /
+// 16: packed float16 14.4 / 15.4 -> 12.9 / 14.4 us; float32 24.5 -> 24.0 at 8.
+// WIDE (matrix-core form): tiles of 32 columns, two adjacent ones per thread,
+// one workgroup per CU (it needs more than 64 registers): 15.9 -> 15.4; packed
+// float16 gains nothing from it (14.5 at 16 blocks, 16.4 at 4).  A reduction of
+// the powers across lanes in place of the LDS buffer (four DPP steps) cost 25%
+// more VALU instructions and 8% more time.
+template <int LOG2N2, class T, int FORM, bool REAL, bool TWO, bool WIDE>
+__global__ void __launch_bounds__(1 << LOG2N2) __attribute__((amdgpu_waves_per_eu(TWO ? 8 : 4)))
+k3_colinv_detect_fold(K3Args args) {
     using Sh = K3Shape<LOG2N2>;
     constexpr int L = Sh::L;
     constexpr int TPV = Sh::TPV;
-    // floats per row of the power buffer: 16 + 4 pad, 16-byte aligned; REAL:
-    // two powers per column, 32 with no pad (the buffer then fills the FFT
-    // tile exactly) but rotated by 4 (row mod 8) floats, so that the row
-    // reads of the epilogue spread over the banks
-    constexpr int PSTRIDE = REAL ? 32 : 20;
-    auto rot = [](int row, int x) { return (x + 4 * (row & 7)) & 31; };
-    __shared__ __align__(16) char lds_raw[Sh::lds(FORM)];
+    __shared__ __align__(16) char lds_raw[Sh::lds(FORM, WIDE)];
     extern __shared__ uint64_t dyn_u64[];
     uint64_t* hsum = dyn_u64;
-    uint32_t* hcnt = reinterpret_cast<uint32_t*>(dyn_u64 + (a.global_mode ? 0 : a.entries));
-    float2* lds = reinterpret_cast<float2*>(lds_raw);
+    uint32_t* hcnt = reinterpret_cast<uint32_t*>(dyn_u64 + (args.global_mode ? 0 : args.entries));
     constexpr bool H16 = FORM == kFormF16 || FORM == kFormMfma;  // float16 arithmetic
     constexpr bool MX = FORM == kFormMfma && kMxShape<LOG2N2, true>;  // radix-16 sums on matrix cores
-    float* pf = reinterpret_cast<float*>(lds_raw + (H16 ? Sh::kHalfTile : 0));
+    static_assert(!WIDE || (H16 && !REAL), "32-column tiles: float16 arithmetic");
+    constexpr int W = WIDE ? 2 : 1;  // adjacent columns per thread, groups of 16 outputs per row
+    using V = std::conditional_t<WIDE, hh2, std::conditional_t<H16, h2, float2>>;
+    V* const tile = reinterpret_cast<V*>(lds_raw);
+    float* const pf = reinterpret_cast<float*>(lds_raw);
+
+    // The arguments lie in host memory: fetch all of their cache lines now, in
+    // one round trip, for the epilogue's reads (k3_kernarg) to find them.
+    asm volatile("" ::"s"(args.work), "s"(args.inv_pfs), "s"(args.acc_sum), "s"(args.inv_subint));
 
     const int c = threadIdx.x & 15;
     const int j = threadIdx.x >> 4;
-    const int n1 = 1 << a.log2n1;
-    const int log2tiles = a.log2n1 - 4;  // tiles of 16 columns per block
-    const int items = a.nblocks << log2tiles;
-    const int r0 = (int)(a.n_front & 15);
-    const double inv_s = a.subint > 0 ? 1.0 / (double)a.subint : 0.0;
-    const int log2d = __builtin_ctz((unsigned)a.decim);  // decim is a power of two
+    const int n1 = 1 << args.log2n1;
+    const int log2tiles = args.log2n1 - (WIDE ? 5 : 4);  // tiles of 16 W columns per block
+    const int items = args.nblocks << log2tiles;
+    const int r0 = (int)(args.n_front & 15);
 
-    if (!a.global_mode) {
-        for (int i = threadIdx.x; i < a.entries; i += blockDim.x) {
+    if (!args.global_mode) {
+        for (int i = threadIdx.x; i < args.entries; i += blockDim.x) {
             hsum[i] = 0;
             hcnt[i] = 0;
         }
@@ -67,238 +123,279 @@ __global__ void __launch_bounds__(1 << LOG2N2) k3_colinv_detect_fold(K3Args a) {
     const int chunk = (items + 7) >> 3;
     const int it_end = min(items, (xcd + 1) * chunk);
     uint32_t flags = 0;
-    StageBases<LOG2N2, LdsVal<FORM>> tb;
-    tb.load(j, a.tw2);
-    // packed float16: the stage-1 twiddle table follows the power buffer
-    h2* ttab = reinterpret_cast<h2*>(lds_raw + Sh::kHalfTile + Sh::kHalfPf);
-    if constexpr (H16) if (threadIdx.x < 64) fill_twiddle_tables<LOG2N2, 64>(ttab, a.tw2, threadIdx.x);
+    StageBases<LOG2N2, V> tb;
+    tb.load(j, args.tw2);
+    // packed float16: the twiddle tables follow the tile
+    h2* ttab = reinterpret_cast<h2*>(lds_raw + W * Sh::kHalfTile);
+    if constexpr (H16) if (threadIdx.x < 64) fill_twiddle_tables<LOG2N2, 64>(ttab, args.tw2, threadIdx.x);
 
-    // Float16 storage with VALU arithmetic, columns of 2^9 and 2^10: the
-    // next item's column tile is loaded (as float16 pairs) while this one
-    // is transformed and folded, so its latency is not exposed once per
-    // item (the 16 registers are free there: the LDS already limits the
-    // kernel to four waves per SIMD).
-    constexpr bool kPrefetch = (H16 || (FORM == kFormF32 && std::is_same<T, __half2>::value)) &&
-                               (LOG2N2 == 10 || (LOG2N2 == 9 && !REAL));  // (else past 128 registers)
-    h2 nxt[16];
-    auto load_tile = [&](int it, h2(&dst)[16]) {
+    // The column tile of an item, as stored.  Where one workgroup has the CU
+    // (TWO: two share it and hide each other's loads), the next item's tile
+    // is loaded while this one is transformed and folded.  WIDE: a thread's two
+    // columns are one 8-byte access (4-byte aligned), but for the pair that
+    // crosses n1 (r0 odd), whose second column is column 0.
+    constexpr bool kPrefetch = !TWO && LOG2N2 >= 9 && (sizeof(T) == 4 || (LOG2N2 == 10 && !REAL));
+    using Raw = std::conditional_t<WIDE, hh2, std::conditional_t<H16, h2, T>>;
+    auto load_tile = [&](int it, Raw(&dst)[16]) {
         const int bb = it >> log2tiles;
         const int tt = it & ((1 << log2tiles) - 1);
-        const uint32_t cc = opaque((uint32_t)((r0 + 16 * tt + c) & (n1 - 1)));
-        const __half2* const ib =
-            uniform_ptr(reinterpret_cast<const __half2*>(a.work) + ((int64_t)bb << (a.log2n1 + LOG2N2)));
-        // the block through a buffer descriptor: the lane's offset in a
-        // vector register, the row offset of value e in a scalar one
-        const BufRes rb = buf_res(ib, (uint32_t)sizeof(__half2) << (a.log2n1 + LOG2N2));
-        if constexpr (MX) {
-            // matrix-core layout: value e = 4b + t at position
-            // 4 (j / 4) + b + (4 (j mod 4) + t) TPV
-            const uint32_t ioff =
-                (cc + ((uint32_t)(4 * (j >> 2) + 4 * (j & 3) * TPV) << a.log2n1)) * (uint32_t)sizeof(__half2);
+        const uint32_t cc = opaque((uint32_t)((r0 + W * (16 * tt + c)) & (n1 - 1)));
+        const T* const ib = uniform_ptr(reinterpret_cast<const T*>(args.work) + ((int64_t)bb << (args.log2n1 + LOG2N2)));
+        // matrix-core layout: value e = 4b + t at position
+        // 4 (j / 4) + b + (4 (j mod 4) + t) TPV
+        const uint32_t ioff =
+            (cc + ((uint32_t)(MX ? 4 * (j >> 2) + 4 * (j & 3) * TPV : j) << args.log2n1)) * (uint32_t)sizeof(T);
+        auto row = [](int e) { return MX ? (e >> 2) + (e & 3) * TPV : TPV * e; };
+        if constexpr (sizeof(T) == 4) {
+            // the block through a buffer descriptor: the lane's offset in a
+            // vector register, the row offset of value e in a scalar one
+            const BufRes rb = buf_res(ib, (uint32_t)sizeof(T) << (args.log2n1 + LOG2N2));
+            if constexpr (WIDE) {
+                if ((r0 & 1) == 0 || 32 * tt + 32 + r0 <= n1) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                dst[e] = buf_ld<h2>(rb, ioff, (int)(((e >> 2) + (e & 3) * TPV) * sizeof(__half2)) << a.log2n1);
+                    for (int e = 0; e < 16; ++e)
+                        dst[e] = buf_ld<hh2>(rb, ioff, (int)(row(e) * sizeof(T)) << args.log2n1);
+                } else {
+                    // r0 odd, last tile: the second column of a pair may be column 0
+                    const uint32_t ioff1 = ioff + (cc + 1 < (uint32_t)n1 ? 1u : 1u - (uint32_t)n1) * (uint32_t)sizeof(T);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int so = (int)(row(e) * sizeof(T)) << args.log2n1;
+                        dst[e] = hh2{buf_ld<h2>(rb, ioff, so), buf_ld<h2>(rb, ioff1, so)};
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) dst[e] = buf_ld<Raw>(rb, ioff, (int)(row(e) * sizeof(T)) << args.log2n1);
+            }
         } else {
-            const uint32_t ioff = (cc + ((uint32_t)j << a.log2n1)) * (uint32_t)sizeof(__half2);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) dst[e] = buf_ld<h2>(rb, ioff, (int)(TPV * e * sizeof(__half2)) << a.log2n1);
+            for (int e = 0; e < 16; ++e) dst[e] = *at(ib + ((int64_t)(TPV * e) << args.log2n1), ioff);
         }
     };
+    Raw nxt[16];
     if constexpr (kPrefetch) {
         if (xcd * chunk + local < it_end) load_tile(xcd * chunk + local, nxt);
     }
+    constexpr int G = REAL ? 32 : 16;  // fold samples of a group
+    constexpr int U = REAL ? 2 : 1;    // per element
     for (int item = xcd * chunk + local; item < it_end; item += per_xcd) {
         const int b = item >> log2tiles;
         const int t = item & ((1 << log2tiles) - 1);
-        const int col = (r0 + 16 * t + c) & (n1 - 1);
-
-        const T* in = reinterpret_cast<const T*>(a.work) + ((int64_t)b << (a.log2n1 + LOG2N2));
-        const uint32_t o0 = opaque((uint32_t)col);
-        if constexpr (H16) {
-            // Packed float16 inverse transform (unnormalised; matrix-core
-            // form: radix-16 sums on the matrix cores), then the power in
-            // float32 from the float16 pair (exact products).
-            h2* lh = reinterpret_cast<h2*>(lds);
-            h2 v[16];
-            if constexpr (kPrefetch) {
+        V v[16];
+        if constexpr (!kPrefetch) load_tile(item, nxt);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = nxt[e];
-                if (item + per_xcd < it_end) load_tile(item + per_xcd, nxt);
-            } else {
-                load_tile(item, v);
-            }
-            // no barrier before the first exchange: every wave has left the
-            // previous item's transform (the barrier after its powers)
-            if constexpr (MX) fft_mx<LOG2N2, +1, false, true, false>(v, j, lh + c, ttab);
-            else fft_wg<LOG2N2, +1, false, 2, false>(v, j, tb, ColLds<h2, true>{lh + c}, ttab);
+        for (int e = 0; e < 16; ++e) {
+            if constexpr (H16) v[e] = nxt[e];
+            else v[e] = Elem<T>::load(&nxt[e]);
+        }
+        if constexpr (kPrefetch) {
+            if (item + per_xcd < it_end) load_tile(item + per_xcd, nxt);
+        }
+        if constexpr (MX && WIDE) {
+            // one column at a time, each in its own tile
+            h2* const t0 = reinterpret_cast<h2*>(lds_raw);
+            h2 x[16], y[16];
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float yx = (float)v[e].x, yy = (float)v[e].y;
-                pf[k3h_pidx(j + TPV * e, c)] = fmaf(yx, yx, yy * yy) * a.pscale;
+                x[e] = v[e].a;
+                y[e] = v[e].b;
             }
-            __syncthreads();
+            fft_mx<LOG2N2, +1, false, true, true>(x, j, t0 + c, ttab);
+            fft_mx<LOG2N2, +1, false, true, false>(y, j, t0 + 16 * L + c, ttab);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = hh2{x[e], y[e]};
+        } else if constexpr (MX) {
+            fft_mx<LOG2N2, +1, false, true, true>(v, j, tile + c, ttab);
+        } else if constexpr (H16) {
+            fft_wg<LOG2N2, +1, false, 2>(v, j, tb, ColSwz<V>{tile + c}, ttab);
         } else {
-            float2 v[16];
-            if constexpr (kPrefetch) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = to_f2(nxt[e]);
-                if (item + per_xcd < it_end) load_tile(item + per_xcd, nxt);
-            } else {
-                const T* const ib = uniform_ptr(in);
-                const uint32_t ioff = (o0 + ((uint32_t)j << a.log2n1)) * (uint32_t)sizeof(T);
-#pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = Elem<T>::load(at(ib + ((int64_t)(TPV * e) << a.log2n1), ioff));
-            }
-            fft_wg<LOG2N2, +1>(v, j, tb, ColLds<float2>{lds + c});
-
-            // Detected powers to LDS, one row of 16 columns per output row.
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float2 y = cscale(v[e], a.scale);
-                if constexpr (REAL) {
-                    const int row = j + TPV * e;
-                    *reinterpret_cast<float2*>(pf + row * PSTRIDE + rot(row, 2 * c)) = make_float2(y.x * y.x, y.y * y.y);
-                } else {
-                    pf[(j + TPV * e) * PSTRIDE + c] = fmaf(y.x, y.x, y.y * y.y);
-                }
-            }
-            __syncthreads();
+            fft_wg<LOG2N2, +1>(v, j, tb, ColSwz<V>{tile + c});
         }
 
-        // Thread q takes group q: outputs n = r0 + 16 t + n1 q + [0, 16),
-        // i.e. 16 consecutive kept outputs (columns that wrap past n1 hold
-        // them one row further down).
-        const int q = threadIdx.x;
-        const int64_t nstart = (int64_t)(r0 + 16 * t) + ((int64_t)q << a.log2n1);
-        const int64_t off = nstart - a.n_front;
-        float p[16];
-        float pr[REAL ? 32 : 1];  // REAL: the 32 real-sample powers of the group
-        if constexpr (REAL) {
-            if (r0 + 16 * t + 15 < n1) {
+        // Detected powers to LDS once every thread has left the transform:
+        // rows of 16 powers, or 32 (WIDE: of 32 columns; REAL: two per column).
+        __syncthreads();
+        K3Kernarg& a = k3_kernarg();
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float4 x4 = *reinterpret_cast<const float4*>(pf + q * PSTRIDE + rot(q, 4 * i));
-                    pr[4 * i] = x4.x;
-                    pr[4 * i + 1] = x4.y;
-                    pr[4 * i + 2] = x4.z;
-                    pr[4 * i + 3] = x4.w;
+        for (int e = 0; e < 16; ++e) {
+            const int row = j + TPV * e;
+            // float16: in float32 from the pair (exact products)
+            auto power = [&](h2 y) {
+                const float yx = (float)y.x, yy = (float)y.y;
+                return fmaf(yx, yx, yy * yy) * a.pscale;
+            };
+            if constexpr (WIDE) {
+                *reinterpret_cast<float2*>(pf + k3_pidx32(row, 2 * c)) = make_float2(power(v[e].a), power(v[e].b));
+            } else if constexpr (H16) {
+                pf[k3_pidx(row, c)] = power(v[e]);
+            } else {
+                const float2 y = cscale(v[e], a.scale);
+                if constexpr (REAL)
+                    *reinterpret_cast<float2*>(pf + k3_pidx32(row, 2 * c)) = make_float2(y.x * y.x, y.y * y.y);
+                else
+                    pf[k3_pidx(row, c)] = fmaf(y.x, y.x, y.y * y.y);
+            }
+        }
+        __syncthreads();
+
+        // Thread q takes row q: W groups of 16 consecutive kept outputs n = r0 +
+        // 16 (W t + g) + n1 q + [0, 16) (columns that wrap past n1 hold them one
+        // row further down).
+        const int q = threadIdx.x;
+#pragma unroll 1
+        for (int g = 0; g < W; ++g) {
+            const int col0 = r0 + 16 * (W * t + g);
+            const int off0 = col0 - (int)a.n_front;
+            const int off = off0 + (q << a.log2n1);
+            if (off < 0 || off >= (int)a.hop) continue;
+            auto pidx = [&](int row, int x) {
+                return WIDE || REAL ? k3_pidx32(row, x + 16 * g) : k3_pidx(row, x);
+            };
+            float p[16];
+            float pr[REAL ? 32 : 1];  // REAL: the 32 real-sample powers of the group
+            if (col0 + 15 < n1) {
+                if constexpr (REAL) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float4 x4 = *reinterpret_cast<const float4*>(pf + pidx(q, 4 * i));
+                        pr[4 * i] = x4.x;
+                        pr[4 * i + 1] = x4.y;
+                        pr[4 * i + 2] = x4.z;
+                        pr[4 * i + 3] = x4.w;
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float4 x4 = *reinterpret_cast<const float4*>(pf + pidx(q, 4 * i));
+                        p[4 * i] = x4.x;
+                        p[4 * i + 1] = x4.y;
+                        p[4 * i + 2] = x4.z;
+                        p[4 * i + 3] = x4.w;
+                    }
                 }
             } else {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int rsrc = q + ((r0 + 16 * t + i) >> a.log2n1);
-                    pr[2 * i] = rsrc < L ? pf[rsrc * PSTRIDE + rot(rsrc, 2 * i)] : 0.f;
-                    pr[2 * i + 1] = rsrc < L ? pf[rsrc * PSTRIDE + rot(rsrc, 2 * i) + 1] : 0.f;
+                    const int row = q + ((col0 + i) >> a.log2n1);
+                    if constexpr (REAL) {
+                        pr[2 * i] = row < L ? pf[pidx(row, 2 * i)] : 0.f;
+                        pr[2 * i + 1] = row < L ? pf[pidx(row, 2 * i + 1)] : 0.f;
+                    } else {
+                        p[i] = row < L ? pf[pidx(row, i)] : 0.f;
+                    }
                 }
             }
+            if constexpr (REAL) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) p[i] = pr[2 * i] + pr[2 * i + 1];
-        } else if (r0 + 16 * t + 15 < n1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float4 x4 = *reinterpret_cast<const float4*>(
-                    pf + (H16 ? k3h_pidx(q, 4 * i) : q * PSTRIDE + 4 * i));
-                p[4 * i] = x4.x;
-                p[4 * i + 1] = x4.y;
-                p[4 * i + 2] = x4.z;
-                p[4 * i + 3] = x4.w;
+                for (int i = 0; i < 16; ++i) p[i] = pr[2 * i] + pr[2 * i + 1];
             }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int rsrc = q + ((r0 + 16 * t + i) >> a.log2n1);
-                p[i] = rsrc < L ? pf[H16 ? k3h_pidx(rsrc, i) : rsrc * PSTRIDE + i] : 0.f;
-            }
-        }
-        if (off < 0 || off >= a.hop) continue;
 
-        // Group sum and the decimated series (sums of `decim` consecutive
-        // powers, pairwise).
-        float s2[8], s4[4], s8[2];
+            // Group sum and the decimated series (sums of `decim` consecutive
+            // powers, pairwise).
+            float s2[8], s4[4], s8[2];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s2[i] = p[2 * i] + p[2 * i + 1];
+            for (int i = 0; i < 8; ++i) s2[i] = p[2 * i] + p[2 * i + 1];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s4[i] = s2[2 * i] + s2[2 * i + 1];
-        s8[0] = s4[0] + s4[1];
-        s8[1] = s4[2] + s4[3];
-        const float s16 = s8[0] + s8[1];
-        const int64_t m0 = (a.block0 + b) * a.hop + off;  // first output of the group
-        if (a.series) {
-            float* sp = a.series + ((m0 >> log2d) - a.series_base);
-            if (a.decim == 16) {
-                sp[0] = s16;
-            } else if (a.decim == 8) {
-                sp[0] = s8[0];
-                sp[1] = s8[1];
-            } else if (a.decim == 4) {
+            for (int i = 0; i < 4; ++i) s4[i] = s2[2 * i] + s2[2 * i + 1];
+            s8[0] = s4[0] + s4[1];
+            s8[1] = s4[2] + s4[3];
+            const float s16 = s8[0] + s8[1];
+            const int64_t mb = (a.block0 + b) * a.hop + off0;  // a multiple of 16
+            const int64_t m0 = mb + ((int64_t)q << a.log2n1);  // first output of the group
+            if (a.series) {
+                const int log2d = __builtin_ctz((unsigned)a.decim);  // decim is a power of two
+                float* const sp = a.series + ((mb >> log2d) - a.series_base) + ((int64_t)q << (a.log2n1 - log2d));
+                if (a.decim == 16) {
+                    sp[0] = s16;
+                } else if (a.decim == 8) {
+                    sp[0] = s8[0];
+                    sp[1] = s8[1];
+                } else if (a.decim == 4) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sp[i] = s4[i];
-            } else if (a.decim == 2) {
+                    for (int i = 0; i < 4; ++i) sp[i] = s4[i];
+                } else if (a.decim == 2) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) sp[i] = s2[i];
-            } else {
+                    for (int i = 0; i < 8; ++i) sp[i] = s2[i];
+                } else {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) sp[i] = p[i];
+                    for (int i = 0; i < 16; ++i) sp[i] = p[i];
+                }
             }
-        }
-        if (!isfinite(s16)) flags |= 1u;
+            if (!isfinite(s16)) flags |= 1u;
+            if (!(s16 < (float)kFoldRangeLimit)) flags |= 2u;
 
-        // Fold: one contribution when all outputs of the group share pulse,
-        // bin and sub-integration (the first and last decide, phase being
-        // monotone).
-        double t0, t15;
-        constexpr int G = REAL ? 32 : 16;  // fold samples of the group
-        const int64_t f0i = REAL ? 2 * m0 : m0, fnf = REAL ? 2 * a.n_front : a.n_front;
-        const int bin0 = fold_bin(f0i, fnf, a.inv_pfs, a.nbins, &t0);
-        const int bin15 = fold_bin(f0i + G - 1, fnf, a.inv_pfs, a.nbins, &t15);
-        const int64_t d0 = m0 - a.s_base * a.subint;
-        const int64_t sub0 = a.subint > 0 ? subint_rel(d0, a.subint, inv_s) : 0;
-        // the group's 16 outputs share sub0 unless it ends within them
-        const bool one_sub = a.subint <= 0 || d0 - sub0 * a.subint + 15 < a.subint;
-        if (bin0 == bin15 && t0 == t15 && one_sub) {
-            fold_add(a, hsum, hcnt, sub0, bin0, s16, G, flags);
-            continue;
-        }
-        // Phase grows with the sample index, so each (pulse, bin) cell holds
-        // consecutive samples: bisect for the end of the first cell (with
-        // the per-sample float64 evaluation itself) and, if the rest of the
-        // group is one cell, add two partial sums; otherwise (a bin shorter
-        // than the group, or a sub-integration edge) one add per sample.
-        int hi = G - 1;
-        bool two = one_sub;
-        if (two) {
-            int lo = 0;
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                double tm;
-                const int bm = fold_bin(f0i + mid, fnf, a.inv_pfs, a.nbins, &tm);
-                if (bm == bin0 && tm == t0) lo = mid;
-                else hi = mid;
+            // Fold: one contribution when all outputs of the group share pulse,
+            // bin and sub-integration.  (The element indices are exact in
+            // float64, so x0 is fold_bin's phase; a phase within fold_safe of
+            // the next bin only fails the test.)
+            const uint64_t fx = fold_fixed(s16);
+            const double x0 = fma((double)(q << a.log2n1), (double)U, (double)(U * (mb + a.n_front))) * a.inv_pfs;
+            const double fl = floor(x0);
+            const double y0 = (x0 - fl) * a.nbins_d;
+            const int bin0 = min((int)y0, a.nbins - 1);
+            const double next = (double)(bin0 + 1);
+            // Sub-integration of the group, if the launch spans more than one;
+            // its 16 outputs share it unless it ends within them.
+            int sub0 = 0;
+            bool one_sub = true;
+            const int64_t d0 = m0 - a.s_base * a.subint;
+            if (a.subint > 0 && a.entries != a.nbins) {
+                sub0 = (int)subint_rel(d0, a.subint, a.inv_subint);
+                one_sub = d0 - sub0 * a.subint + 15 < a.subint;
             }
-            double th;
-            const int bh = fold_bin(f0i + hi, fnf, a.inv_pfs, a.nbins, &th);
-            two = bh == bin15 && th == t15;
-        }
-        if (two) {
-            float sa = 0.f, sb = 0.f;
+            if (one_sub && y0 + fma(x0, a.fold_safe1, a.fold_safe0) < next) {
+                k3_fold_add(a, hsum, hcnt, sub0, bin0, fx, G);
+                continue;
+            }
+            // Otherwise by the per-sample float64 evaluation itself.
+            const int64_t f0i = U * m0, fnf = U * a.n_front;
+            double t15;
+            const int bin15 = fold_bin(f0i + G - 1, fnf, a.inv_pfs, a.nbins, &t15);
+            if (one_sub && bin0 == bin15 && fl == t15) {
+                k3_fold_add(a, hsum, hcnt, sub0, bin0, fx, G);
+                continue;
+            }
+            // Phase grows with the sample index, so each (pulse, bin) cell holds
+            // consecutive samples.  Two cells (the bin is longer than the
+            // group): the first ends before sample `hi`, estimated from the phase
+            // and checked on both sides; two partial sums.
+            if (one_sub) {
+                // (where a bin is a whole number of samples, rounding decides
+                // whose the boundary sample is: the estimate takes the lower one)
+                int hi = max(1, min(G - 1, (int)ceil((next - y0) * a.samples_per_bin - 1e-3)));
+                double ta, tb2;
+                const int ba = fold_bin(f0i + hi - 1, fnf, a.inv_pfs, a.nbins, &ta);
+                int bb = fold_bin(f0i + hi, fnf, a.inv_pfs, a.nbins, &tb2);
+                if (bb == bin0 && tb2 == fl) {
+                    ++hi;  // below G: the last sample is in another cell
+                    bb = fold_bin(f0i + hi, fnf, a.inv_pfs, a.nbins, &tb2);
+                }
+                if (ba == bin0 && ta == fl && bb == bin15 && tb2 == t15) {
+                    float sa = 0.f;
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                const float v = REAL ? pr[i] : p[i];
-                sa += i < hi ? v : 0.f;
-                sb += i < hi ? 0.f : v;
+                    for (int i = 0; i < G; ++i) sa += i < hi ? (REAL ? pr[i] : p[i]) : 0.f;
+                    const uint64_t fa = fold_fixed(sa);
+                    k3_fold_add(a, hsum, hcnt, sub0, bin0, fa, (uint32_t)hi);
+                    k3_fold_add(a, hsum, hcnt, sub0, bin15, fx - fa, (uint32_t)(G - hi));
+                    continue;
+                }
             }
-            fold_add(a, hsum, hcnt, sub0, bin0, sa, (uint32_t)hi, flags);
-            fold_add(a, hsum, hcnt, sub0, bin15, sb, (uint32_t)(G - hi), flags);
-        } else {
+            // A bin shorter than the group, a sub-integration edge, or an
+            // estimate further off: one add per sample (from LDS again: no
+            // thread writes there before the next item's first barrier).
             for (int i = 0; i < G; ++i) {
+                const int ci = REAL ? i >> 1 : i;
+                const int row = q + ((col0 + ci) >> a.log2n1);
+                const float pi = row >= L ? 0.f : pf[pidx(row, i)];
                 double ti;
                 const int bi = fold_bin(f0i + i, fnf, a.inv_pfs, a.nbins, &ti);
-                const int64_t si = a.subint > 0 ? subint_rel(d0 + (REAL ? i / 2 : i), a.subint, inv_s) : 0;
-                fold_add(a, hsum, hcnt, si, bi, REAL ? pr[i] : p[i], 1, flags);
+                const int si = a.subint > 0 ? (int)subint_rel(d0 + ci, a.subint, a.inv_subint) : 0;
+                k3_fold_add(a, hsum, hcnt, si, bi, fold_fixed(pi), 1);
             }
         }
     }
+    K3Kernarg& a = k3_kernarg();
     if (flags) atomicOr(a.status, flags);
     if (!a.global_mode) {
         __syncthreads();
@@ -311,14 +408,47 @@ __global__ void __launch_bounds__(1 << LOG2N2) k3_colinv_detect_fold(K3Args a) {
     }
 }
 
+template <class T, int FORM, int LOG2N2, bool REAL, bool TWO, bool WIDE = false>
+static hipError_t k3_launch(const K3Args& a, int grid, size_t dyn, hipStream_t s) {
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&k3_colinv_detect_fold<LOG2N2, T, FORM, REAL, TWO, WIDE>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)(160 * 1024 - K3Shape<LOG2N2>::lds(FORM, WIDE)));
+    if (attr != hipSuccess) return attr;
+    K3Args c = a;
+    const double per_sample = a.inv_pfs * (double)a.nbins;  // bins per sample
+    c.nbins_d = (double)a.nbins;
+    c.fold_safe0 = (REAL ? 31 : 15) * per_sample + 1e-9;
+    c.fold_safe1 = 1e-15 * (double)a.nbins;
+    c.samples_per_bin = 1.0 / per_sample;
+    c.inv_subint = a.subint > 0 ? 1.0 / (double)a.subint : 0.0;
+    hipLaunchKernelGGL((k3_colinv_detect_fold<LOG2N2, T, FORM, REAL, TWO, WIDE>), dim3(grid), dim3(1 << LOG2N2), dyn,
+                       s, c);
+    return hipGetLastError();
+}
+
+// 32-column tiles (items: of 16 columns): the float16-arithmetic forms' columns
+// of 2^10, where they leave an item for every CU and the histogram fits beside
+// them.
+constexpr int64_t kWideItems = 256;
+static bool k3_wide(bool mfma, int log2n2, int64_t items, size_t dyn) {
+    return mfma && log2n2 == 10 && items / 2 >= kWideItems && K3Shape<10>::LDS_WIDE + dyn <= kLdsBytes;
+}
+
 template <class T, int FORM, int LOG2N2>
 static hipError_t k3_one(const K3Args& a, int grid, size_t dyn, hipStream_t s) {
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k3_colinv_detect_fold<LOG2N2, T, FORM>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)(160 * 1024 - K3Shape<LOG2N2>::lds(FORM)));
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((k3_colinv_detect_fold<LOG2N2, T, FORM>), dim3(grid), dim3(1 << LOG2N2), dyn, s, a);
-    return hipGetLastError();
+    if constexpr (FORM == kFormMfma && LOG2N2 == 10) {
+        if (k3_wide(true, LOG2N2, (int64_t)a.nblocks << (a.log2n1 - 4), dyn))
+            return k3_launch<T, FORM, LOG2N2, false, false, true>(a, grid, dyn, s);
+    }
+    // Packed float16, columns of 2^9 and 2^10: two (four) workgroups share a CU
+    // at 64 registers, unless the histogram leaves no room for two.  (Shorter
+    // columns fit four to a CU either way, and the matrix-core form needs more
+    // registers than that.)
+    if constexpr (FORM == kFormF16 && LOG2N2 >= 9) {
+        if (2 * (K3Shape<LOG2N2>::lds(FORM) + dyn) <= kLdsBytes)
+            return k3_launch<T, FORM, LOG2N2, false, true>(a, grid, dyn, s);
+    }
+    return k3_launch<T, FORM, LOG2N2, false, false>(a, grid, dyn, s);
 }
 
 template <class T, int FORM>
@@ -334,25 +464,15 @@ static hipError_t k3_dispatch(int log2n2, const K3Args& a, int grid, size_t dyn,
     }
 }
 
-template <class T, int LOG2N2>
-static hipError_t k3_real_one(const K3Args& a, int grid, size_t dyn, hipStream_t s) {
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k3_colinv_detect_fold<LOG2N2, T, kFormF32, true>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)(160 * 1024 - K3Shape<LOG2N2>::LDS));
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((k3_colinv_detect_fold<LOG2N2, T, kFormF32, true>), dim3(grid), dim3(1 << LOG2N2), dyn, s, a);
-    return hipGetLastError();
-}
-
 template <class T>
 static hipError_t k3_real_dispatch(int log2n2, const K3Args& a, int grid, size_t dyn, hipStream_t s) {
     switch (log2n2) {
-        case 5: return k3_real_one<T, 5>(a, grid, dyn, s);
-        case 6: return k3_real_one<T, 6>(a, grid, dyn, s);
-        case 7: return k3_real_one<T, 7>(a, grid, dyn, s);
-        case 8: return k3_real_one<T, 8>(a, grid, dyn, s);
-        case 9: return k3_real_one<T, 9>(a, grid, dyn, s);
-        case 10: return k3_real_one<T, 10>(a, grid, dyn, s);
+        case 5: return k3_launch<T, kFormF32, 5, true, false>(a, grid, dyn, s);
+        case 6: return k3_launch<T, kFormF32, 6, true, false>(a, grid, dyn, s);
+        case 7: return k3_launch<T, kFormF32, 7, true, false>(a, grid, dyn, s);
+        case 8: return k3_launch<T, kFormF32, 8, true, false>(a, grid, dyn, s);
+        case 9: return k3_launch<T, kFormF32, 9, true, false>(a, grid, dyn, s);
+        case 10: return k3_launch<T, kFormF32, 10, true, false>(a, grid, dyn, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -382,7 +502,9 @@ int64_t hist_capacity(int log2n2, int prec) {
 
 int k3_grid(int log2n2, int prec, size_t dyn_lds, int64_t items, int64_t entries, bool global_mode,
             int64_t part_entries) {
-    const size_t lds = k3_static_lds(log2n2, prec) + dyn_lds;
+    const bool wide = k3_wide(prec == kMixed, log2n2, items, dyn_lds);
+    if (wide) items /= 2;
+    const size_t lds = (wide ? K3Shape<10>::LDS_WIDE : k3_static_lds(log2n2, prec)) + dyn_lds;
     int per_cu = (int)(kLdsBytes / lds);
     per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
     int64_t grid = 256 * per_cu;
