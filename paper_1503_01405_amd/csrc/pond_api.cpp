@@ -4,6 +4,7 @@
 // batch of overlap-save blocks, then the profile finalisation.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -75,6 +76,7 @@ struct pond_plan {
     int log2n = 0, log2n1 = 0, log2n2 = 0, hbits = 0;
     int32_t nbins = 0, precision = 0;
     int max_batch = 1;
+    int launch_batch = 1;       // blocks per launch of a call, at most max_batch
     size_t elem = 8;
     // Real two-channel input (Sec. 3.1: channels A and B added in phase):
     // element m packs real samples 2m, 2m+1; every count above is in
@@ -373,6 +375,29 @@ int default_max_batch(int64_t nfft, int32_t precision, int32_t max_batch) {
     return (int)(b < 1 ? 1 : (b > 16 ? 16 : b));
 }
 
+// Blocks per launch of a plan that left them to the library: its max_batch,
+// or fewer where that keeps the work area in the 256 MB Infinity Cache from
+// one pass to the next (beside the row table, which every launch reads), so
+// that the later passes read it from there.  Half of the cache, but at least 3
+// blocks, below which the column passes have too few tiles per workgroup.
+// Measured, ms of a stream in launches of so many blocks: packed float16 2^23
+// (32 MB a block) 4 blocks 5.26, 16 5.75, 2 6.12; 2^22 8 blocks 2.25, 16 2.38;
+// float32 2^23 3 blocks 9.27, 8 9.70, 2 9.50; 2^22 4 blocks 3.51, 16 3.65.
+// Longer rows (2^24) gain nothing (matrix-core 2 blocks 6.87, 8 6.48), the split
+// middle pass of 2^25 and more, which crosses the work area five times, runs
+// best one block at a time (packed float16 2^25: 9.13, 4 blocks 10.85).  Real
+// input reads twice the table: only float32 up to 2^22 gains (packed 2^21, 8
+// blocks 4.12, 16 4.84).
+int cached_batch(int64_t nfft, int32_t precision, int32_t kind, int max_batch) {
+    const int64_t elem = precision == POND_FP32 ? 8 : 4;
+    const int log2n = ilog2(nfft);
+    if (kind != POND_INPUT_COMPLEX && (precision != POND_FP32 || log2n > 22)) return max_batch;
+    if (log2n == 24) return max_batch;
+    if (log2n > 24) return 1;
+    const int64_t fit = ((int64_t)1 << 27) / (nfft * elem);
+    return (int)std::min<int64_t>(max_batch, std::max<int64_t>(3, fit));
+}
+
 int64_t n_blocks_for(int64_t nsamp, int64_t nfft, int64_t hop) {
     return nsamp < nfft ? 0 : (nsamp - nfft) / hop + 1;
 }
@@ -618,6 +643,8 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     p->precision = precision;
     p->elem = precision == POND_FP32 ? 8 : 4;
     const bool autotune = max_batch == POND_BATCH_AUTOTUNE;
+    // (acc_slots: the server's plans, whose max_batch is what its budget left)
+    const bool chosen = acc_slots == 0 && (max_batch > 0 || (autotune && kind == POND_INPUT_COMPLEX));
     p->max_batch = max_batch = default_max_batch(nfft, precision, max_batch);
 
     p->hist_cap = hist_capacity(p->log2n2, p->precision);
@@ -675,6 +702,7 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     chk(hipMalloc(reinterpret_cast<void**>(&p->part_cnt), (size_t)kPartEntries * 4));
     chk(hipMalloc(reinterpret_cast<void**>(&p->status), 8));
     if (e == hipSuccess && autotune && kind == POND_INPUT_COMPLEX) chk(tune_plan(p));
+    p->launch_batch = chosen ? p->max_batch : cached_batch(nfft, precision, kind, p->max_batch);
     chk(hipMalloc(&p->work, (size_t)p->max_batch * (size_t)nfft * p->elem));
     // Float16 arithmetic (packed float16 and matrix-core forms): the power
     // scale is 256 over the measured gain of the plan's float16 arithmetic
@@ -1027,7 +1055,7 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     ReduceQueue rq;
     int64_t rq_blocks = 0;  // blocks whose fold partials are queued
     while (b < nb_total) {
-        int64_t nb = nb_total - b < p->max_batch ? nb_total - b : p->max_batch;
+        int64_t nb = nb_total - b < p->launch_batch ? nb_total - b : p->launch_batch;
         int64_t s_lo = 0, nsub = 1;
         for (;;) {
             if (subint > 0) {
