@@ -16,11 +16,23 @@ namespace pond {
 // group takes AID_TS consecutive output times and keeps their powers in
 // registers; the workgroup then writes them channel-major, F[c][t], through
 // an LDS transpose (rows of ROWS*AID_TS consecutive times per channel).
-constexpr int AID_TS = 4;
+// Bound: VALU (about 50 instructions per sample).  512 threads and two times
+// per group (LDS 68 KB, at most 128 registers) give 16 waves per CU; with 256
+// threads and four times 64 of 150 registers held powers and 8 waves ran.  The
+// next spectrum's samples are read during a transform.
+constexpr int AID_TS = 2;
+template <int LOG2C>
+struct AidShape {
+    static constexpr int TPV = (1 << LOG2C) / 16;
+    static constexpr int THREADS = 512;
+    static constexpr int ROWS = THREADS / TPV;
+    static constexpr int STRIDE = (1 << LOG2C) + (1 << LOG2C) / 16;
+};
 
 template <int LOG2C>
-__global__ void __launch_bounds__(K2Shape<LOG2C>::THREADS) aid_filterbank(AidArgs a) {
-    using Sh = K2Shape<LOG2C>;
+__global__ void __launch_bounds__(AidShape<LOG2C>::THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+aid_filterbank(AidArgs a) {
+    using Sh = AidShape<LOG2C>;
     constexpr int C = 1 << LOG2C;
     constexpr int TPV = Sh::TPV;
     constexpr int ROWS = Sh::ROWS;
@@ -37,23 +49,32 @@ __global__ void __launch_bounds__(K2Shape<LOG2C>::THREADS) aid_filterbank(AidArg
     StageBases<LOG2C> tb;
     tb.load(j, a.tw);
     const int64_t tbase = (int64_t)blockIdx.x * COLS;
-
+    // the group's spectra are consecutive blocks of C samples; output times
+    // past the last re-read its blocks and are not stored
+    const int64_t t0 = tbase + g * AID_TS;
+    const int nspec = AID_TS * a.nint;
+    const int64_t last = a.nspec * a.nint - 1;  // last block of the input
+    uint32_t raw[16];
+    auto load = [&](int k) {
+        const int64_t blk = min(t0 * a.nint + k, last);
+        const int8_t* p = a.iq + 2 * blk * (int64_t)C;
+        const uint32_t o = opaque((uint32_t)j);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) raw[e] = *at(reinterpret_cast<const uint16_t*>(p), (o + TPV * e) * 2u);
+    };
+    load(0);
     float acc[AID_TS][16];
 #pragma unroll
     for (int ts = 0; ts < AID_TS; ++ts) {
-        const int64_t t = tbase + g * AID_TS + ts;
-        const bool live = t < a.nspec;
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[ts][e] = 0.f;
         for (int i = 0; i < a.nint; ++i) {
             float2 v[16];
-            const int8_t* blk = a.iq + 2 * ((live ? t : 0) * a.nint + i) * (int64_t)C;
-            const uint32_t o = opaque((uint32_t)j);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const short sv = *at(reinterpret_cast<const short*>(blk), (o + TPV * e) * 2u);
-                v[e] = make_float2((float)(int8_t)(sv & 0xff), (float)(int8_t)(sv >> 8));
-            }
+            for (int e = 0; e < 16; ++e)
+                v[e] = make_float2((float)(int8_t)(raw[e] & 0xff), (float)(int8_t)((raw[e] >> 8) & 0xff));
+            const int next = ts * a.nint + i + 1;
+            if (next < nspec) load(next);
             fft_wg<LOG2C, -1>(v, j, tb, lrow);
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[ts][e] = fmaf(v[e].x, v[e].x, fmaf(v[e].y, v[e].y, acc[ts][e]));
@@ -61,12 +82,11 @@ __global__ void __launch_bounds__(K2Shape<LOG2C>::THREADS) aid_filterbank(AidArg
     }
     __syncthreads();  // the FFT scratch becomes the transpose tile
 #pragma unroll
-    for (int ts = 0; ts < AID_TS; ++ts)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) tile[(j + TPV * e) * COLS + g * AID_TS + ts] = acc[ts][e];
+    for (int e = 0; e < 16; ++e)
+        *reinterpret_cast<float2*>(tile + (j + TPV * e) * COLS + g * AID_TS) = make_float2(acc[0][e], acc[1][e]);
     __syncthreads();
     const int64_t ncols = a.nspec - tbase < COLS ? a.nspec - tbase : COLS;
-    for (int idx = threadIdx.x; idx < C * COLS; idx += blockDim.x) {
+    for (int idx = threadIdx.x; idx < C * COLS; idx += Sh::THREADS) {
         const int c = idx / COLS, col = idx - c * COLS;
         if (col < ncols) a.F[(int64_t)c * a.nspec + tbase + col] = tile[idx];
     }
@@ -117,7 +137,7 @@ __global__ void __launch_bounds__(256) aid_dedisperse_fold(AidArgs a) {
 
 template <int LOG2C>
 static hipError_t aid_fb_one(const AidArgs& a, hipStream_t s) {
-    using Sh = K2Shape<LOG2C>;
+    using Sh = AidShape<LOG2C>;
     const int64_t cols = Sh::ROWS * AID_TS;
     const int64_t grid = (a.nspec + cols - 1) / cols;
     if (grid <= 0) return hipSuccess;

@@ -378,6 +378,7 @@ struct StageBases<LOG2L, hh2> : StageBases<LOG2L, float2> {};
 template <class V, bool PAD = false>
 struct ColLds {
     V* base;
+    static constexpr bool kRow = false;
     static constexpr uint32_t kSlots(uint32_t n) { return PAD ? n * 16 + 4 * (n / 4) : n * 16; }
     static __device__ __forceinline__ uint32_t idx(uint32_t p) { return PAD ? p * 16 + 4 * (p >> 2) : p * 16; }
     template <int D, bool AL = false>
@@ -401,6 +402,7 @@ struct ColLds {
 template <class V>
 struct ColSwz {
     V* base;
+    static constexpr bool kRow = false;
     template <int D, bool AL = false>
     __device__ __forceinline__ V* addr(int p0) const {
         const uint32_t u = (uint32_t)p0;
@@ -424,6 +426,7 @@ struct ColSwz {
 template <class V>
 struct PadLds {
     V* base;
+    static constexpr bool kRow = true;
     template <int D, bool AL = false>
     __device__ __forceinline__ V* addr(int p0) const {
         if constexpr (D % 16 == 0 || AL) {
@@ -449,6 +452,7 @@ struct PadLds {
 template <class V>
 struct StageRowLds {
     V* base;
+    static constexpr bool kRow = true;
     template <int S>
     struct At {
         V* base;
@@ -747,10 +751,28 @@ __device__ __forceinline__ void stage_tw_tab(const h2* tab, int j, h2 (&t)[16]) 
     }
 }
 
+// Order the LDS accesses of the threads that share a vector: the workgroup's
+// barrier, or, where the vector lies in one wave, nothing but the program order
+// (a wave's LDS operations complete in order).
+template <bool WAVE>
+__device__ __forceinline__ void vector_sync() {
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
+}
+// Rows of up to 2^10 are one wave's (or a part of one): their transforms need
+// no workgroup barriers.
+template <int LOG2L>
+constexpr bool kWaveRow = LOG2L <= 10;
+
 // Full length-L transform (DIR = -1 forward, +1 inverse, unnormalised) of
 // the vector held by thread j.  lds is the vector's LDS layout (ColLds or
 // PadLds); every thread of the workgroup must call this together
-// (it contains barriers).  With HALF_NORM (float16 forward transforms)
+// (it contains barriers, but for rows of one wave).  With HALF_NORM (float16 forward transforms)
 // every even stage but the first scales its input by 1/16 (the caller
 // scales the first stage's input and applies the remaining 2^-kHalfRem).
 // Float16 transforms read their stage twiddles from the LDS tables ttab
@@ -771,6 +793,7 @@ __device__ __forceinline__ void fft_wg(V (&v)[16], int j, const StageBases<LOG2L
     constexpr int L = 1 << LOG2L;
     constexpr int TPV = L / 16;
     constexpr bool HALF = kIsHalf<V>;
+    constexpr bool WAVE = Lds::kRow && kWaveRow<LOG2L>;
     static_for<S::kStages>([&](auto si) {
         constexpr int s = decltype(si)::value;
         constexpr int R = S::radix(s);
@@ -793,10 +816,10 @@ __device__ __forceinline__ void fft_wg(V (&v)[16], int j, const StageBases<LOG2L
         }
         if constexpr (!LAST) {
             const auto st = stage_view<s>(lds);
-            if constexpr (s > 0 || LEAD) __syncthreads();
+            if constexpr (s > 0 || LEAD) vector_sync<WAVE>();
             stockham_stage<L, R, NS, DIR, false, SC>(v, j, base, st, tw);
             if constexpr (s == S::kStages - 2) hook();
-            __syncthreads();
+            vector_sync<WAVE>();
             static_for<16>([&](auto ei) {
                 constexpr int e = decltype(ei)::value;
                 v[e] = st.template get<TPV * e>(j);

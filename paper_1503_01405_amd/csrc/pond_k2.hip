@@ -169,6 +169,7 @@ k2_row(K2Args a) {
         // stage 1's for the packed-float16 form (its other stages form their
         // twiddles from float32 powers, which measures faster here)
         if (threadIdx.x < 64) fill_twiddle_tables<LOG2N1, 64, !MX>(ttab, a.tw1, threadIdx.x);
+        if constexpr (!MX && kWaveRow<LOG2N1>) __syncthreads();  // (no barrier before the tables' first use)
         const uint2* tab = reinterpret_cast<const uint2*>(a.htable) + ((int64_t)row0 << LOG2N1);
         const h2* tw4 = reinterpret_cast<const h2*>(a.htw4) + ((int64_t)row0 << LOG2N1);
         const h2* chirp = reinterpret_cast<const h2*>(a.hchirp) + ((int64_t)row0 << LOG2N1);
@@ -418,6 +419,7 @@ k2_row_inv(K2Args a) {
     T* dst = reinterpret_cast<T*>(a.out) + (int64_t)bfirst * bstep + row_at;
     if constexpr (F16) {
         if (threadIdx.x < 64) fill_twiddle_tables<LOG2N1, 64, !MX>(ttab, a.tw1, threadIdx.x);
+        if constexpr (!MX && kWaveRow<LOG2N1>) __syncthreads();  // (no barrier before the tables' first use)
     }
     // element of the workgroup's rows held at register e on input
     auto in_u = [](int e) { return MX ? 16 * (e >> 2) + (e & 3) * TPV : TPV * e; };

@@ -112,6 +112,8 @@ k2_real_pair(RealPairArgs a) {
             v[e] = cadd(cmul(own[e], v[e]), partner ? cneg(x) : x);
         });
     }
+    // the partner has read this row (rows of one wave have no barrier of their own)
+    if constexpr (kWaveRow<LOG2N1>) __syncthreads();
     // output twiddles fetched during the last exchange
     float2 wo[16];
     auto fetch_tw = [&] {
