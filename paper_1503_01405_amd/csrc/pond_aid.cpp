@@ -200,9 +200,15 @@ int64_t pond_aid_run(pond_aid* a, const int8_t* iq, int64_t nsamp, float* profil
         if (e != hipSuccess) return fail();
     }
     if (nout > 0) {
-        int64_t grid = (nout + 255) / 256;
+        // 16 waves for every CU, of 64 outputs each, sharing outputs if there
+        // are too few and the sums fit beside the histogram; 16 waves to a
+        // workgroup, at most two workgroups per CU
+        const int64_t tiles = (nout + 63) / 64;
+        if (aid_sum_lds(a->nbins, a->nchan, 1) <= (size_t)kAidSumLds)
+            while (g.log2split < 4 && tiles << g.log2split < 16 * 256) ++g.log2split;
+        int64_t grid = ((tiles << g.log2split) + 15) / 16;
         const int64_t cap = kPartEntries / a->nbins;
-        grid = grid < 2048 ? grid : 2048;
+        grid = grid < 512 ? grid : 512;
         grid = grid < cap ? grid : cap;
         grid = grid < 1 ? 1 : grid;
         e = launch_aid_dedisperse_fold(g, (int)grid, stream);

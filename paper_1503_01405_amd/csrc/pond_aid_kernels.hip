@@ -96,10 +96,20 @@ aid_filterbank(AidArgs a) {
 // dd_c = d_c - d_min >= 0 (Eq. (3) delays in integrated samples); the
 // series value and its fold into integer (sub-integration-free) histograms
 // as K3 does, fold phase x = (m - d_min) * nchan * nint * inv_pfs.
-__global__ void __launch_bounds__(256) aid_dedisperse_fold(AidArgs a) {
+// A wave takes 64 consecutive outputs and 1 / 2^log2split of the channels; the
+// waves of a workgroup that share outputs meet in LDS.  Bound: reading F (60 s of
+// 1024 channels: 960 MB).  One output per thread over all channels left the chip
+// idle on short segments of many channels.  Whole calls, before and now: 4,882
+// outputs of 4,096 channels 476 and 121 us (16 ways); 7,812 of 512, 73 and 32
+// (16); 117,187 of 128, 83.5 and 80.7 (4); 468,750 of 64, 82.5 and 79.7 (none:
+// the barriers of 16 ways cost it 116); 234,375 of 1,024, 1,385 and 1,356 (2).
+constexpr int AID_SUM_THREADS = 1024;
+__global__ void __launch_bounds__(AID_SUM_THREADS) aid_dedisperse_fold(AidArgs a) {
+    constexpr int WAVES = AID_SUM_THREADS / 64;
     extern __shared__ uint64_t dyn_u64[];
-    uint64_t* hsum = dyn_u64;
-    uint32_t* hcnt = reinterpret_cast<uint32_t*>(dyn_u64 + a.nbins);
+    float* part = reinterpret_cast<float*>(dyn_u64);  // [WAVES][64], with a split only
+    uint64_t* hsum = dyn_u64 + (a.log2split > 0 ? WAVES * 32 : 0);
+    uint32_t* hcnt = reinterpret_cast<uint32_t*>(hsum + a.nbins);
     int32_t* dd = reinterpret_cast<int32_t*>(hcnt + a.nbins);
     for (int i = threadIdx.x; i < a.nbins; i += blockDim.x) {
         hsum[i] = 0;
@@ -109,21 +119,37 @@ __global__ void __launch_bounds__(256) aid_dedisperse_fold(AidArgs a) {
     __syncthreads();
     uint32_t flags = 0;
     const double spec = (double)a.nchan * (double)a.nint;
-    for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < a.nout;
-         m += (int64_t)gridDim.x * blockDim.x) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int share = wave & ((1 << a.log2split) - 1);  // which of the channels
+    const int per_wave = a.nchan >> a.log2split;
+    const int64_t step = (int64_t)64 * (WAVES >> a.log2split);  // outputs per workgroup at a time
+    for (int64_t base = (int64_t)blockIdx.x * step; base < a.nout; base += (int64_t)gridDim.x * step) {
+        const int64_t m = base + 64 * (wave >> a.log2split) + lane;
         float s = 0.f;
-        const float* f = a.F + m;
-        for (int c = 0; c < a.nchan; ++c) s += f[(int64_t)c * a.nspec + dd[c]];
-        if (a.series) a.series[m] = s;
-        const double x = (double)(m - a.d_min) * spec * a.inv_pfs;
-        int bin = (int)((x - floor(x)) * (double)a.nbins);
-        bin = bin < a.nbins - 1 ? bin : a.nbins - 1;
-        const double dv = (double)s * kFoldScale;
-        if (!(dv < kFoldRangeLimit * kFoldScale)) flags |= 2u;
-        if (!isfinite(s)) flags |= 1u;
-        const uint64_t fx = isfinite(s) ? (uint64_t)__double2ull_rn(dv) : 0ull;
-        atomicAdd((unsigned long long*)&hsum[bin], (unsigned long long)fx);
-        atomicAdd(&hcnt[bin], 1u);
+        if (m < a.nout) {
+            const float* f = a.F + m;
+#pragma unroll 8
+            for (int c = share * per_wave; c < (share + 1) * per_wave; ++c) s += f[(int64_t)c * a.nspec + dd[c]];
+        }
+        if (a.log2split > 0) {
+            __syncthreads();  // the previous outputs' sums have been read
+            part[wave * 64 + lane] = s;
+            __syncthreads();
+        }
+        if (share == 0 && m < a.nout) {
+            for (int w = 1; w < 1 << a.log2split; ++w) s += part[(wave + w) * 64 + lane];
+            if (a.series) a.series[m] = s;
+            const double x = (double)(m - a.d_min) * spec * a.inv_pfs;
+            int bin = (int)((x - floor(x)) * (double)a.nbins);
+            bin = bin < a.nbins - 1 ? bin : a.nbins - 1;
+            const double dv = (double)s * kFoldScale;
+            if (!(dv < kFoldRangeLimit * kFoldScale)) flags |= 2u;
+            if (!isfinite(s)) flags |= 1u;
+            const uint64_t fx = isfinite(s) ? (uint64_t)__double2ull_rn(dv) : 0ull;
+            atomicAdd((unsigned long long*)&hsum[bin], (unsigned long long)fx);
+            atomicAdd(&hcnt[bin], 1u);
+        }
     }
     if (flags) atomicOr(a.status, flags);
     __syncthreads();
@@ -159,11 +185,11 @@ hipError_t launch_aid_filterbank(int log2c, const AidArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_aid_dedisperse_fold(const AidArgs& a, int grid, hipStream_t s) {
-    const size_t dyn = (size_t)a.nbins * 12 + (size_t)a.nchan * 4;
+    const size_t dyn = aid_sum_lds(a.nbins, a.nchan, a.log2split);
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&aid_dedisperse_fold),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kAidSumLds);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(aid_dedisperse_fold, dim3(grid), dim3(256), dyn, s, a);
+    hipLaunchKernelGGL(aid_dedisperse_fold, dim3(grid), dim3(AID_SUM_THREADS), dyn, s, a);
     return hipGetLastError();
 }
 

@@ -176,6 +176,7 @@ struct AidArgs {
     const int32_t* dd;      // [nchan] delay minus the smallest delay (integrated samples)
     int32_t d_min;          // smallest delay
     int64_t nout;           // dedispersed outputs
+    int32_t log2split;      // waves that share an output's channels (at most 16)
     float* series;          // [nout] or NULL
     int32_t nbins;
     double inv_pfs;         // 1 / (period * fs)
@@ -184,6 +185,11 @@ struct AidArgs {
     uint32_t* status;
 };
 hipError_t launch_aid_filterbank(int log2c, const AidArgs& a, hipStream_t s);
+// LDS of the channel sum: histogram, delays and, with a split, 16 waves' sums.
+constexpr int kAidSumLds = 160 * 1024;
+inline size_t aid_sum_lds(int nbins, int nchan, int log2split) {
+    return (size_t)nbins * 12 + (size_t)nchan * 4 + (log2split > 0 ? 16 * 64 * 4 : 0);
+}
 hipError_t launch_aid_dedisperse_fold(const AidArgs& a, int grid, hipStream_t s);
 
 // Launchers; each returns the HIP error of the launch.

@@ -57,3 +57,23 @@ def test_aid_too_short_stream():
     iq = synth.white_stream_int8(3, 2_000_000)  # 488 integrated samples < 746 of delay span
     prof, ser, geo = _gpu_aid(iq, nchan, nint, dm, 64, 0.0891)
     assert geo["n_series"] == 0 and ser.size == 0 and np.all(prof == 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nchan,nint,nsamp", [(64, 1, 64 * 65), (64, 1, 17_000_011), (128, 1, 9_000_000),
+                                              (1024, 1, 70 * 1024), (1024, 2, 3_000_001), (4096, 1, 4096 * 3),
+                                              (4096, 3, 2_000_000)])
+def test_gpu_channel_sum_splits(nchan, nint, nsamp):
+    """Outputs shared by 1 to 16 waves, the last tile of 64 ragged."""
+    import torch
+    import paper_1503_01405_amd as P
+    iq = synth.white_stream_int8(81, nsamp)
+    want = O.aid_run(iq, 326.5, 16.0, 0.3, nchan, nint, 32, 0.0017)
+    h = P.pond_aid_create(326.5, 16.0, 0.3, nchan, nint, 32, 0.0017)
+    n = want["series"].size
+    prof, ser = torch.empty(32, device="cuda"), torch.empty(max(n, 1), device="cuda")
+    assert P.pond_aid_run(h, torch.from_numpy(iq).cuda(), nsamp, prof, ser, n) == n
+    torch.cuda.synchronize()
+    P.pond_aid_destroy(h)
+    for got, ref in ((ser.cpu().numpy()[:n], want["series"]), (prof.cpu().numpy(), want["profile"])):
+        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
