@@ -25,8 +25,6 @@ struct pond_aid {
     int32_t* dd = nullptr;
     float* F = nullptr;
     size_t F_cap = 0;  // floats
-    uint64_t* acc_sum = nullptr;
-    uint64_t* acc_cnt = nullptr;
     uint64_t* part_sum = nullptr;
     uint32_t* part_cnt = nullptr;
     uint64_t* status = nullptr;
@@ -37,7 +35,7 @@ struct pond_aid {
 namespace {
 
 void free_aid(pond_aid* a) {
-    void* ptrs[] = {a->tw, a->dd, a->F, a->acc_sum, a->acc_cnt, a->part_sum, a->part_cnt, a->status};
+    void* ptrs[] = {a->tw, a->dd, a->F, a->part_sum, a->part_cnt, a->status};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
 }
@@ -113,8 +111,6 @@ pond_aid* pond_aid_create(double f0_mhz, double bw_mhz, double dm, int32_t nchan
     };
     chk(hipMalloc(reinterpret_cast<void**>(&a->tw), (size_t)nchan * sizeof(float2)));
     chk(hipMalloc(reinterpret_cast<void**>(&a->dd), (size_t)nchan * 4));
-    chk(hipMalloc(reinterpret_cast<void**>(&a->acc_sum), (size_t)nbins * 8));
-    chk(hipMalloc(reinterpret_cast<void**>(&a->acc_cnt), (size_t)nbins * 8));
     chk(hipMalloc(reinterpret_cast<void**>(&a->part_sum), (size_t)kPartEntries * 8));
     chk(hipMalloc(reinterpret_cast<void**>(&a->part_cnt), (size_t)kPartEntries * 4));
     chk(hipMalloc(reinterpret_cast<void**>(&a->status), 8));
@@ -176,9 +172,7 @@ int64_t pond_aid_run(pond_aid* a, const int8_t* iq, int64_t nsamp, float* profil
         a->F = nf;
         a->F_cap = need;
     }
-    hipError_t e = launch_zero_u64(a->acc_sum, a->nbins, stream);
-    if (e == hipSuccess) e = launch_zero_u64(a->acc_cnt, a->nbins, stream);
-    if (e != hipSuccess) return fail();
+    hipError_t e = hipSuccess;
     AidArgs g{};
     g.iq = iq;
     g.nspec = nspec;
@@ -199,6 +193,7 @@ int64_t pond_aid_run(pond_aid* a, const int8_t* iq, int64_t nsamp, float* profil
         e = launch_aid_filterbank(a->log2c, g, stream);
         if (e != hipSuccess) return fail();
     }
+    int64_t grid = 0;
     if (nout > 0) {
         // 16 waves for every CU, of 64 outputs each, sharing outputs if there
         // are too few and the sums fit beside the histogram; 16 waves to a
@@ -206,17 +201,15 @@ int64_t pond_aid_run(pond_aid* a, const int8_t* iq, int64_t nsamp, float* profil
         const int64_t tiles = (nout + 63) / 64;
         if (aid_sum_lds(a->nbins, a->nchan, 1) <= (size_t)kAidSumLds)
             while (g.log2split < 4 && tiles << g.log2split < 16 * 256) ++g.log2split;
-        int64_t grid = ((tiles << g.log2split) + 15) / 16;
+        grid = ((tiles << g.log2split) + 15) / 16;
         const int64_t cap = kPartEntries / a->nbins;
         grid = grid < 512 ? grid : 512;
         grid = grid < cap ? grid : cap;
         grid = grid < 1 ? 1 : grid;
         e = launch_aid_dedisperse_fold(g, (int)grid, stream);
-        if (e == hipSuccess)
-            e = launch_fold_reduce(a->part_sum, a->part_cnt, (int)grid, a->nbins, a->acc_sum, a->acc_cnt, 0, stream);
         if (e != hipSuccess) return fail();
     }
-    e = launch_fold_profiles(a->acc_sum, a->acc_cnt, a->nbins, profile, stream);
+    e = launch_fold_reduce_profile(a->part_sum, a->part_cnt, (int)grid, a->nbins, profile, stream);
     if (e != hipSuccess) return fail();
     a->last_stream = stream;
     return done(nout);

@@ -977,10 +977,11 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
         const int64_t nprof = in_open > 0 ? 1 : 0;
         if (nprof > max_profiles || (nprof && !profiles)) return POND_EINVAL;
         if (nprof) {
-            e = timed(4, 0, [&] { return launch_fold_finalize(p->acc_sum, p->acc_cnt, nbins, 1, 1, profiles, stream); });
-            if (e != hipSuccess) return fail(e);
+            e = timed(4, 0, [&] { return launch_fold_finalize(p->acc_sum, p->acc_cnt, nbins, 1, 1, profiles, p->status,
+                                                                stream); });
+        } else {
+            e = launch_zero_u64(p->status, 1, stream);
         }
-        e = launch_zero_u64(p->status, 1, stream);
         if (e != hipSuccess) return fail(e);
         p->samples_in = 0;
         p->blocks_done = 0;
@@ -1185,7 +1186,7 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     if (n_complete > 0) {
         e = timed(4, 0, [&] {
             return launch_fold_finalize(p->acc_sum, p->acc_cnt, nbins, (int)n_complete, (int)n_touched, profiles,
-                                        stream);
+                                        nullptr, stream);
         });
         if (e != hipSuccess) return fail(e);
     }
@@ -1193,26 +1194,14 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     // Keep the samples future blocks need: absolute [nb_total * hop, total).
     const int64_t new_start = nb_total * hop;
     int8_t* dst = p->tail[p->tcur ^ 1];
-    int64_t filled = 0;
-    if (p->samples_in > new_start) {
-        const int64_t from = new_start > p->tail_start ? new_start : p->tail_start;
-        const int64_t cnt = p->samples_in - from;
-        if (cnt > 0) {
-            e = hipMemcpyAsync(dst, p->tail[p->tcur] + p->bpe * (from - p->tail_start), (size_t)cnt * p->bpe,
-                               hipMemcpyDeviceToDevice, stream);
-            if (e != hipSuccess) return fail(e);
-            filled = cnt;
-        }
-    }
-    {
-        const int64_t from = new_start > p->samples_in ? new_start : p->samples_in;
-        const int64_t cnt = total - from;
-        if (cnt > 0) {
-            e = hipMemcpyAsync(dst + p->bpe * filled, iq + p->bpe * (from - p->samples_in), (size_t)cnt * p->bpe,
-                               hipMemcpyDeviceToDevice, stream);
-            if (e != hipSuccess) return fail(e);
-        }
-    }
+    // from the previous tail (before this call's first sample), then from iq
+    const int64_t from_tail = std::max(new_start, p->tail_start);
+    const int64_t from_iq = std::max(new_start, p->samples_in);
+    const int64_t n_tail = std::max<int64_t>(p->samples_in - from_tail, 0);
+    const int64_t n_iq = std::max<int64_t>(total - from_iq, 0);
+    e = launch_carry_tail(dst, p->tail[p->tcur] + (n_tail ? p->bpe * (from_tail - p->tail_start) : 0), p->bpe * n_tail,
+                          n_iq ? iq + p->bpe * (from_iq - p->samples_in) : iq, p->bpe * n_iq, stream);
+    if (e != hipSuccess) return fail(e);
     p->tcur ^= 1;
     p->tail_start = new_start;
     p->samples_in = total;

@@ -14,6 +14,13 @@
 
 namespace pond {
 
+// exp(-2 pi i t / n): float64 sine and cosine rounded to float32.
+__device__ __forceinline__ float2 stage_twiddle(int64_t t, int64_t n) {
+    double sn, cs;
+    sincospi(2.0 * (double)t / (double)n, &sn, &cs);
+    return make_float2((float)cs, (float)-sn);
+}
+
 // --------------------------------------------------------- storage forms
 template <class T>
 struct Elem;

@@ -11,46 +11,13 @@
 namespace pond {
 
 // ------------------------------------------------------ fold reduction
-// Sum the per-workgroup partial histograms (integer, so order-free) and
-// add them to the accumulators.  Grid: x over entries, y over part chunks.
-// The partials were just written and sit in cache: a full chunk issues all
-// its loads at once, so a call costs about one load latency, not a chain.
+// Sum the per-workgroup partial histograms (integer, so order-free) of up to
+// kReduceSlots queued launches and add them to the accumulators.  Grid: x over
+// entries, y over part chunks, z the launch; each has its own partials,
+// accumulators and sizes.  The partials were just written and sit in cache: a
+// full chunk issues all its loads at once, so a call costs about one load
+// latency, not a chain.
 constexpr int kReduceChunk = 8;
-__global__ void __launch_bounds__(256) fold_reduce(const uint64_t* __restrict__ ps, const uint32_t* __restrict__ pc,
-                                                   int nparts, int entries, uint64_t* acc_sum, uint64_t* acc_cnt,
-                                                   int64_t acc_off) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= entries) return;
-    const int p0 = blockIdx.y * kReduceChunk;
-    const int p1 = min(nparts, p0 + kReduceChunk);
-    uint64_t s = 0, n = 0;
-    if (p1 - p0 == kReduceChunk) {
-        uint64_t sv[kReduceChunk];
-        uint32_t nv[kReduceChunk];
-#pragma unroll
-        for (int k = 0; k < kReduceChunk; ++k) {
-            sv[k] = ps[(int64_t)(p0 + k) * entries + i];
-            nv[k] = pc[(int64_t)(p0 + k) * entries + i];
-        }
-#pragma unroll
-        for (int k = 0; k < kReduceChunk; ++k) {
-            s += sv[k];
-            n += nv[k];
-        }
-    } else {
-        for (int q = p0; q < p1; ++q) {
-            s += ps[(int64_t)q * entries + i];
-            n += pc[(int64_t)q * entries + i];
-        }
-    }
-    if (n) {
-        atomicAdd((unsigned long long*)&acc_sum[acc_off + i], (unsigned long long)s);
-        atomicAdd((unsigned long long*)&acc_cnt[acc_off + i], (unsigned long long)n);
-    }
-}
-
-// The same for up to kReduceSlots queued launches at once (blockIdx.z
-// picks the launch; each has its own partials, accumulators and sizes).
 __global__ void __launch_bounds__(256) fold_reduce_batch(ReduceBatch b) {
     const ReduceJob& j = b.job[blockIdx.z];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -87,12 +54,47 @@ __global__ void __launch_bounds__(256) fold_reduce_batch(ReduceBatch b) {
     }
 }
 
+// The partials of the only launch of a call, summed straight into its profile
+// (a call that accumulates over launches goes through fold_reduce_batch).  A
+// workgroup takes 16 bins (128 bytes of a partial's sums) and reads 64 partials
+// at once: the bound is the latency of these loads (7,812 filterbank outputs,
+// whole call: 31.4 us with the four launches that cleared two accumulators, added
+// to them and divided, 28.2 with this one).
+constexpr int kProfileBins = 16;
+__global__ void __launch_bounds__(1024) fold_reduce_profile(const uint64_t* __restrict__ ps,
+                                                            const uint32_t* __restrict__ pc, int nparts, int nbins,
+                                                            float* profile) {
+    constexpr int PARTS = 1024 / kProfileBins;
+    __shared__ uint64_t sum[PARTS][kProfileBins], cnt[PARTS][kProfileBins];
+    const int lane = threadIdx.x % kProfileBins, part = threadIdx.x / kProfileBins;
+    const int bin = blockIdx.x * kProfileBins + lane;
+    uint64_t s = 0, n = 0;
+    if (bin < nbins) {
+#pragma unroll 8
+        for (int q = part; q < nparts; q += PARTS) {
+            s += ps[(int64_t)q * nbins + bin];
+            n += pc[(int64_t)q * nbins + bin];
+        }
+    }
+    sum[part][lane] = s;
+    cnt[part][lane] = n;
+    __syncthreads();
+    if (part > 0 || bin >= nbins) return;
+    for (int w = 1; w < PARTS; ++w) {
+        s += sum[w][lane];
+        n += cnt[w][lane];
+    }
+    profile[bin] = n ? (float)(((double)s / kFoldScale) / (double)n) : 0.f;
+}
+
 // Write the profiles of the first n_complete slots, then move slot
 // n_complete (the still-open sub-integration, if any) to slot 0 and clear
-// the rest of the n_touched slots.  One thread per bin.
+// the rest of the n_touched slots.  One thread per bin.  A status word is
+// cleared beside it (the end of a stream: not a launch of its own).
 __global__ void __launch_bounds__(256) fold_finalize(uint64_t* acc_sum, uint64_t* acc_cnt, int nbins, int n_complete,
-                                                     int n_touched, float* profiles) {
+                                                     int n_touched, float* profiles, uint64_t* status) {
     const int bin = blockIdx.x * blockDim.x + threadIdx.x;
+    if (status && bin == 0) *status = 0;
     if (bin >= nbins) return;
     for (int k = 0; k < n_complete; ++k) {
         const uint64_t s = acc_sum[(int64_t)k * nbins + bin];
@@ -123,6 +125,26 @@ __global__ void __launch_bounds__(256) fold_profiles(const uint64_t* acc_sum, co
     profiles[i] = c ? (float)(((double)acc_sum[i] / kFoldScale) / (double)c) : 0.f;
 }
 
+// The na bytes at a, then the nb at b, to dst: the samples that the next blocks
+// need, from the previous carry and from this call's input.  dst is 16-byte
+// aligned, the sources need not be.  Bound: the launch on short calls (300,007
+// samples and the flush: 61.9 us with two copy commands and a launch that only
+// cleared the status word, 60.2 without).
+__global__ void __launch_bounds__(256) carry_tail(int8_t* __restrict__ dst, const int8_t* __restrict__ a, int64_t na,
+                                                  const int8_t* __restrict__ b, int64_t nb) {
+    const int64_t o = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 16;
+    const int64_t total = na + nb;
+    if (o >= total) return;
+    if (o + 16 <= total && (o + 16 <= na || o >= na)) {
+        struct Word { uint32_t w[4]; } v;
+        __builtin_memcpy(&v, o >= na ? b + (o - na) : a + o, 16);
+        *reinterpret_cast<uint4*>(dst + o) = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
+    } else {
+        const int64_t end = o + 16 < total ? o + 16 : total;
+        for (int64_t k = o; k < end; ++k) dst[k] = k < na ? a[k] : b[k - na];
+    }
+}
+
 // Streaming copy of n16 16-byte words (measurement of the achievable HBM
 // bandwidth): each workgroup moves contiguous 16 KB chunks, a thread's four
 // loads of a chunk in flight before its stores.
@@ -146,14 +168,11 @@ __global__ void __launch_bounds__(256) copy_u128(u32x4* __restrict__ dst, const 
     }
 }
 
-// Stage twiddles of a length-n transform: w[t] = exp(-2 pi i t / n) for
-// t < count, float64 sine and cosine rounded to float32.
+// Stage twiddles of a length-n transform for t < count.
 __global__ void __launch_bounds__(256) stage_twiddles(float2* w, int64_t count, int64_t n) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= count) return;
-    double sn, cs;
-    sincospi(2.0 * (double)t / (double)n, &sn, &cs);
-    w[t] = make_float2((float)cs, (float)-sn);
+    w[t] = stage_twiddle(t, n);
 }
 
 // Pseudo-random bytes (splitmix64 of the word index and a seed, Steele,
@@ -172,10 +191,10 @@ __global__ void __launch_bounds__(256) zero_u64(uint64_t* p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
-hipError_t launch_fold_reduce(const uint64_t* ps, const uint32_t* pc, int nparts, int entries, uint64_t* acc_sum,
-                              uint64_t* acc_cnt, int64_t acc_off, hipStream_t s) {
-    dim3 grid((entries + 255) / 256, (nparts + kReduceChunk - 1) / kReduceChunk);
-    hipLaunchKernelGGL(fold_reduce, grid, dim3(256), 0, s, ps, pc, nparts, entries, acc_sum, acc_cnt, acc_off);
+hipError_t launch_fold_reduce_profile(const uint64_t* ps, const uint32_t* pc, int nparts, int nbins, float* profile,
+                                      hipStream_t s) {
+    hipLaunchKernelGGL(fold_reduce_profile, dim3((nbins + kProfileBins - 1) / kProfileBins), dim3(1024), 0, s,
+                       ps, pc, nparts, nbins, profile);
     return hipGetLastError();
 }
 
@@ -193,9 +212,16 @@ hipError_t launch_fold_reduce_batch(const ReduceBatch& b, hipStream_t s) {
 }
 
 hipError_t launch_fold_finalize(uint64_t* acc_sum, uint64_t* acc_cnt, int nbins, int n_complete, int n_touched,
-                                float* profiles, hipStream_t s) {
+                                float* profiles, uint64_t* status, hipStream_t s) {
     hipLaunchKernelGGL(fold_finalize, dim3((nbins + 255) / 256), dim3(256), 0, s, acc_sum, acc_cnt, nbins,
-                       n_complete, n_touched, profiles);
+                       n_complete, n_touched, profiles, status);
+    return hipGetLastError();
+}
+
+hipError_t launch_carry_tail(int8_t* dst, const int8_t* a, int64_t na, const int8_t* b, int64_t nb, hipStream_t s) {
+    if (na + nb <= 0) return hipSuccess;
+    const int64_t words = (na + nb + 15) / 16;
+    hipLaunchKernelGGL(carry_tail, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, dst, a, na, b, nb);
     return hipGetLastError();
 }
 

@@ -196,16 +196,29 @@ hipError_t launch_aid_dedisperse_fold(const AidArgs& a, int grid, hipStream_t s)
 hipError_t launch_k1(int prec, int log2n2, const K1Args& a, hipStream_t s);
 hipError_t launch_k2(int prec, int mode, int log2n1, const K2Args& a, hipStream_t s);
 hipError_t launch_k3(int prec, int log2n2, const K3Args& a, int grid, size_t dyn_lds, hipStream_t s);
-hipError_t launch_fold_reduce(const uint64_t* part_sum, const uint32_t* part_cnt, int nparts, int entries,
-                              uint64_t* acc_sum, uint64_t* acc_cnt, int64_t acc_off, hipStream_t s);
+hipError_t launch_fold_reduce_profile(const uint64_t* part_sum, const uint32_t* part_cnt, int nparts, int nbins,
+                                      float* profile, hipStream_t s);
 hipError_t launch_fold_finalize(uint64_t* acc_sum, uint64_t* acc_cnt, int nbins, int n_complete, int n_touched,
-                                float* profiles, hipStream_t s);
+                                float* profiles, uint64_t* status, hipStream_t s);
+hipError_t launch_carry_tail(int8_t* dst, const int8_t* a, int64_t na, const int8_t* b, int64_t nb, hipStream_t s);
 hipError_t launch_copy_u128(void* dst, const void* src, int64_t n16, hipStream_t s);
 hipError_t launch_zero_u64(uint64_t* p, int64_t n, hipStream_t s);
 // n words of pseudo-random bits (splitmix64 of index and seed): timing input.
 hipError_t launch_fill_noise_u64(uint64_t* p, int64_t n, uint64_t seed, hipStream_t s);
 // w[t] = exp(-2 pi i t / n) for t < n, float64 sine/cosine rounded to float32.
 hipError_t launch_stage_twiddles(float2* w, int64_t n, hipStream_t s);
+// What a segment call prepares: row table (float4 or float2 as below), stage
+// twiddles of both passes, cleared words.
+struct SegmentPrep {
+    void* table;
+    float2* tw1;            // [n1]
+    float2* tw2;            // [n2]
+    uint64_t* zero;         // [nzero]
+    int64_t nzero;
+    int32_t log2n1, log2n2;
+    double chirp_a, f0, df;
+};
+hipError_t launch_segment_prep(bool twiddle, const SegmentPrep& a, hipStream_t s);
 // twiddle: float4 entries (twiddle, chirp), else float2 (chirp).
 hipError_t launch_k2_build_table(void* tab, bool twiddle, int log2n1, int log2n2, double chirp_a, double f0,
                                  double df, double taper, hipStream_t s);

@@ -19,12 +19,9 @@ namespace pond {
 // form, whose row kernel forms the twiddle itself).
 // Built once per plan; every block reads the same table.
 template <bool TW>
-__global__ void __launch_bounds__(256) k2_build_table(void* __restrict__ tab, int log2n1, int log2n2, double chirp_a,
-                                                       double f0, double df, double taper) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int log2n = log2n1 + log2n2;
-    const int64_t n = 1ll << log2n;
-    if (i >= n) return;
+__device__ void k2_table_entry(void* __restrict__ tab, int64_t i, int log2n1, int log2n2, double chirp_a, double f0,
+                               double df, double taper) {
+    const int64_t n = 1ll << (log2n1 + log2n2);
     const int64_t k2 = i >> log2n1;
     const int64_t k1 = i & ((1ll << log2n1) - 1);
     const int64_t k = k2 + (k1 << log2n2);
@@ -43,6 +40,37 @@ __global__ void __launch_bounds__(256) k2_build_table(void* __restrict__ tab, in
     } else {
         reinterpret_cast<float2*>(tab)[i] = make_float2((float)(cc * w), (float)(-cs * w));
     }
+}
+
+template <bool TW>
+__global__ void __launch_bounds__(256) k2_build_table(void* __restrict__ tab, int log2n1, int log2n2, double chirp_a,
+                                                       double f0, double df, double taper) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 1ll << (log2n1 + log2n2)) k2_table_entry<TW>(tab, i, log2n1, log2n2, chirp_a, f0, df, taper);
+}
+
+// All that a segment call prepares for itself: the row table (no taper), both
+// stage twiddle tables and nzero cleared words, thread ranges of one launch.
+// Bound: the launch.  With six launches for these and three for the profile a
+// call on 40,001 samples in blocks of 2^12 took 53 us, with one and one 39.
+template <bool TW>
+__global__ void __launch_bounds__(256) segment_prep(SegmentPrep a) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t n = 1ll << (a.log2n1 + a.log2n2);
+    if (i < n) {
+        k2_table_entry<TW>(a.table, i, a.log2n1, a.log2n2, a.chirp_a, a.f0, a.df, 0.0);
+        return;
+    }
+    i -= n;
+    for (int k = 0; k < 2; ++k) {
+        const int64_t len = 1ll << (k ? a.log2n2 : a.log2n1);
+        if (i < len) {
+            (k ? a.tw2 : a.tw1)[i] = stage_twiddle(i, len);
+            return;
+        }
+        i -= len;
+    }
+    if (i < a.nzero) a.zero[i] = 0;
 }
 
 // One workgroup takes row k2 (ROWS rows for short rows) of one block.  The
@@ -725,6 +753,14 @@ hipError_t launch_k2_build_table_h(void* tab, int log2n1, int log2n2, double chi
     const double chirp_scale = std::ldexp(1.0, -half_row_rem(log2n1));
     hipLaunchKernelGGL(k2_build_table_h, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                        reinterpret_cast<uint2*>(tab), log2n1, log2n2, chirp_a, f0, df, chirp_scale, taper);
+    return hipGetLastError();
+}
+
+hipError_t launch_segment_prep(bool twiddle, const SegmentPrep& a, hipStream_t s) {
+    const int64_t n = (1ll << (a.log2n1 + a.log2n2)) + (1ll << a.log2n1) + (1ll << a.log2n2) + a.nzero;
+    const dim3 grid((unsigned)((n + 255) / 256));
+    if (twiddle) hipLaunchKernelGGL(segment_prep<true>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(segment_prep<false>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -116,15 +116,19 @@ int64_t pond_dedisperse_segment_noalloc(double f0_mhz, double bw_mhz, double dm,
         (void)hipGetLastError();
         return POND_EDEVICE;
     };
-    hipError_t e = launch_stage_twiddles(tw1, n1, stream);
-    if (e == hipSuccess) e = launch_stage_twiddles(tw2, n2, stream);
-    if (e == hipSuccess)
-        e = launch_k2_build_table(table, precision != POND_FP32, log2n1, log2n2, dm / (2.41e-10 * f0_mhz * f0_mhz),
-                                  f0_mhz, bw_mhz / (double)nfft, 0.0, stream);
-    // accumulators and status start at zero (fill kernels, no memset nodes)
-    if (e == hipSuccess) e = launch_zero_u64(acc_sum, nbins, stream);
-    if (e == hipSuccess) e = launch_zero_u64(acc_cnt, nbins, stream);
-    if (e == hipSuccess) e = launch_zero_u64(status, 1, stream);
+    SegmentPrep prep{};
+    prep.table = table;
+    prep.tw1 = tw1;
+    prep.tw2 = tw2;
+    // accumulators and status start at zero (a fill kernel, no memset nodes)
+    prep.zero = acc_sum;
+    prep.nzero = (status + 1) - acc_sum;
+    prep.log2n1 = log2n1;
+    prep.log2n2 = log2n2;
+    prep.chirp_a = dm / (2.41e-10 * f0_mhz * f0_mhz);
+    prep.f0 = f0_mhz;
+    prep.df = bw_mhz / (double)nfft;
+    hipError_t e = launch_segment_prep(precision != POND_FP32, prep, stream);
     if (e != hipSuccess) return fail();
 
     const int64_t cap = hist_capacity(log2n2, precision);
@@ -181,11 +185,20 @@ int64_t pond_dedisperse_segment_noalloc(double f0_mhz, double bw_mhz, double dm,
         const size_t dyn = global_mode ? 0 : (size_t)nbins * 12;
         const int grid = k3_grid(log2n2, precision, dyn, (int64_t)nb * (n1 / 16), nbins, global_mode, kPartCap);
         e = launch_k3(precision, log2n2, a3, grid, dyn, stream);
-        if (e == hipSuccess && !global_mode)
-            e = launch_fold_reduce(part_sum, part_cnt, grid, nbins, acc_sum, acc_cnt, 0, stream);
+        if (e != hipSuccess) return fail();
+        if (global_mode) continue;
+        if (nb_total <= max_batch) {  // the only launch: straight to the profile
+            e = launch_fold_reduce_profile(part_sum, part_cnt, grid, nbins, profile, stream);
+            if (e != hipSuccess) return fail();
+            return n_out / decim;
+        }
+        ReduceBatch one;
+        one.job[0] = ReduceJob{part_sum, part_cnt, acc_sum, acc_cnt, 0, (int32_t)grid, (int32_t)nbins};
+        one.n = 1;
+        e = launch_fold_reduce_batch(one, stream);
         if (e != hipSuccess) return fail();
     }
-    e = launch_fold_finalize(acc_sum, acc_cnt, nbins, 1, 1, profile, stream);
+    e = launch_fold_finalize(acc_sum, acc_cnt, nbins, 1, 1, profile, nullptr, stream);
     if (e != hipSuccess) return fail();
     return n_out / decim;
 }
