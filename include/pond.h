@@ -96,7 +96,7 @@ typedef struct pond_info {
     int64_t n1, n2;        /* four-step factorisation nfft = n1 * n2 (row x col)   */
     int64_t samples_in;    /* input samples appended since the stream started     */
     int64_t outputs_done;  /* outputs produced since the stream started           */
-    int64_t max_batch;     /* blocks per launch                                    */
+    int64_t max_batch;     /* blocks per launch, as given, tuned or by default      */
     double  fs_hz;         /* complex sample rate                                  */
     double  delta_lo_s;    /* delay of band bottom relative to f0                  */
     double  delta_hi_s;    /* advance of band top relative to f0                   */
@@ -196,7 +196,9 @@ pond_plan* pond_plan_create(double f0_mhz, double bw_mhz, double dm,
  * plus the default) during creation and
  * keep the fastest per block, a larger launch winning only by more than 0.5%;
  * other values <= 0 pick the default (2^29 bytes of work area, 1 .. 16
- * blocks).  With the environment variable POND_AUTOTUNE_CACHE naming a
+ * blocks; the calls then launch more of the shorter blocks at once, up to 2^27
+ * bytes of work area if the device has them, and fewer of the longer ones where
+ * that keeps the work area cached).  With the environment variable POND_AUTOTUNE_CACHE naming a
  * text file, a choice already measured for the same device, nfft, form,
  * input kind and histogram placement is read from it instead, and new
  * choices are appended (one line each; the last matching line wins).
@@ -396,7 +398,8 @@ pond_search* pond_search_create(double f0_mhz, double bw_mhz, const double* dms,
  * max_batch > 0 as given; POND_BATCH_AUTOTUNE tunes each group as
  * pond_plan_create_ex does (its forward pass and two trials' inverse
  * passes timed on pseudo-random input; POND_AUTOTUNE_CACHE as there);
- * other values <= 0 the default (2^28 bytes of spectrum, 1 .. 16 blocks).
+ * other values <= 0 the default (2^28 bytes of spectrum, 1 .. 16 blocks, or
+ * more of the shorter ones up to 2^26 bytes, if the device has them).
  */
 pond_search* pond_search_create_ex(double f0_mhz, double bw_mhz, const double* dms, int32_t ntrials,
                                    int32_t nbins, double period_s, int64_t nfft_min, int64_t nfft_max,

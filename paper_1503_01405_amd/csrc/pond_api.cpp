@@ -76,7 +76,7 @@ struct pond_plan {
     int log2n = 0, log2n1 = 0, log2n2 = 0, hbits = 0;
     int32_t nbins = 0, precision = 0;
     int max_batch = 1;
-    int launch_batch = 1;       // blocks per launch of a call, at most max_batch
+    int launch_batch = 1;       // blocks per launch of a call
     size_t elem = 8;
     // Real two-channel input (Sec. 3.1: channels A and B added in phase):
     // element m packs real samples 2m, 2m+1; every count above is in
@@ -388,15 +388,24 @@ int default_max_batch(int64_t nfft, int32_t precision, int32_t max_batch) {
 // best one block at a time (packed float16 2^25: 9.13, 4 blocks 10.85).  Real
 // input reads twice the table: only float32 up to 2^22 gains (packed 2^21, 8
 // blocks 4.12, 16 4.84).
+// Short blocks go more than max_batch to a launch, as many as that half holds:
+// 16 blocks of 2^12 are 64 column tiles for 256 CUs.  2 s (32 M samples), in
+// launches of 16 blocks and of the rule's count, us: float32 2^12 17,186 and 695
+// (1,024; the rule 4,096), 2^14 4,913 and 435, 2^16 1,679 and 423, 2^18 463 and
+// 328 (twice the rule 346); packed float16 2^16 1,329 and 300, 2^18 368 and 219;
+// real input of 2^15 points 2,464 and 309, 2^19 234 and 173.
 int cached_batch(int64_t nfft, int32_t precision, int32_t kind, int max_batch) {
     const int64_t elem = precision == POND_FP32 ? 8 : 4;
     const int log2n = ilog2(nfft);
+    const int64_t fit = ((int64_t)1 << 27) / (nfft * elem);
+    if (fit > max_batch) return (int)fit;
     if (kind != POND_INPUT_COMPLEX && (precision != POND_FP32 || log2n > 22)) return max_batch;
     if (log2n == 24) return max_batch;
     if (log2n > 24) return 1;
-    const int64_t fit = ((int64_t)1 << 27) / (nfft * elem);
     return (int)std::min<int64_t>(max_batch, std::max<int64_t>(3, fit));
 }
+
+constexpr int64_t kFullBins = 1024;  // bins of sub-integrations one large launch folds into
 
 int64_t n_blocks_for(int64_t nsamp, int64_t nfft, int64_t hop) {
     return nsamp < nfft ? 0 : (nsamp - nfft) / hop + 1;
@@ -703,7 +712,15 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     chk(hipMalloc(reinterpret_cast<void**>(&p->status), 8));
     if (e == hipSuccess && autotune && kind == POND_INPUT_COMPLEX) chk(tune_plan(p));
     p->launch_batch = chosen ? p->max_batch : cached_batch(nfft, precision, kind, p->max_batch);
-    chk(hipMalloc(&p->work, (size_t)p->max_batch * (size_t)nfft * p->elem));
+    // (a server's plan is charged for max_batch blocks)
+    if (acc_slots > 0) p->launch_batch = std::min(p->launch_batch, p->max_batch);
+    if (p->launch_batch > p->max_batch && e == hipSuccess &&
+        hipMalloc(&p->work, (size_t)p->launch_batch * (size_t)nfft * p->elem) != hipSuccess) {
+        (void)hipGetLastError();
+        p->work = nullptr;
+        p->launch_batch = p->max_batch;  // no room for more
+    }
+    if (!p->work) chk(hipMalloc(&p->work, (size_t)p->max_batch * (size_t)nfft * p->elem));
     // Float16 arithmetic (packed float16 and matrix-core forms): the power
     // scale is 256 over the measured gain of the plan's float16 arithmetic
     // (the unit-taper table just built).
@@ -1064,7 +1081,10 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
                 const int64_t s_hi = ((b + nb) * hop - 1) / subint;
                 nsub = s_hi - s_lo + 1;
             }
-            if (nsub * nbins <= p->hist_cap || nb == 1) break;
+            // beyond max_batch no more bins of several sub-integrations than leave
+            // K3 its workgroups per CU; in global memory any number
+            const int64_t cap = nb > p->max_batch ? std::min(p->hist_cap, std::max<int64_t>(nbins, kFullBins)) : p->hist_cap;
+            if (nbins > p->hist_cap || nsub * nbins <= cap || nb == 1) break;
             nb = (nb + 1) / 2;
         }
         const int64_t entries = nsub * nbins;

@@ -351,8 +351,26 @@ pond_search* pond_search_create_ex(double f0_mhz, double bw_mhz, const double* d
         }
         if (e == hipSuccess) chk(launch_build_dm_geometry(g.geo, g.log2n1, g.log2n2, f0_mhz, df, nullptr));
         if (e == hipSuccess && max_batch == POND_BATCH_AUTOTUNE) chk(tune_group(s, g, g.max_batch));
-        chk(hipMalloc(&g.spec, (size_t)g.max_batch * g.nfft * s->elem));
-        chk(hipMalloc(&g.out, (size_t)g.max_batch * g.nfft * s->elem));
+        // Left to the library, short blocks go as many to a launch as half the
+        // Infinity Cache holds of spectrum and output.  0.25 s, 8 trials, launches
+        // of 16 blocks and of the rule's count, us: packed float16 2^12 11,229 and
+        // 499 (1,024; the rule 4,096), 2^14 2,977 and 373, 2^16 948 and 337, 2^18
+        // 443 and 354; float32 2^16 1,078 and 382.
+        const int fit = (int)(((int64_t)1 << 26) / (g.nfft * (int64_t)s->elem));
+        if (max_batch <= 0 && max_batch != POND_BATCH_AUTOTUNE && fit > g.max_batch && e == hipSuccess) {
+            const size_t bytes = (size_t)fit * g.nfft * s->elem;
+            if (hipMalloc(&g.spec, bytes) == hipSuccess && hipMalloc(&g.out, bytes) == hipSuccess) {
+                g.max_batch = fit;
+            } else {  // no room for more than the usual count
+                (void)hipGetLastError();
+                if (g.spec) (void)hipFree(g.spec);
+                g.spec = g.out = nullptr;
+            }
+        }
+        if (!g.spec) {
+            chk(hipMalloc(&g.spec, (size_t)g.max_batch * g.nfft * s->elem));
+            chk(hipMalloc(&g.out, (size_t)g.max_batch * g.nfft * s->elem));
+        }
         // Packed float16: power scale 256 over the measured gain of the
         // group's float16 path (forward rows, then the inverse rows of the
         // group's first trial; every trial's chirp rounds alike).

@@ -108,7 +108,9 @@ int64_t pond_dedisperse_segment_noalloc(double f0_mhz, double bw_mhz, double dm,
     const size_t block_bytes = (size_t)nfft * elem;
     if (off + block_bytes > kScratchBytes) return POND_EINVAL;
     const int64_t fit = (int64_t)((kScratchBytes - off) / block_bytes);
-    const int max_batch = (int)(fit > 16 ? 16 : fit);
+    // as many blocks a launch as fit: 16 blocks of 2^12 are 64 workgroups
+    // (40,001 samples, 17 blocks of 2^12: 39 us in two launches, 22 in one)
+    const int max_batch = (int)fit;
     void* work = take((size_t)max_batch * block_bytes);
 
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);

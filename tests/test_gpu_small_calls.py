@@ -1,6 +1,7 @@
-"""Launches of short calls: a segment whose blocks take one launch or several,
-its histograms in LDS or not, and samples carried between calls from buffers
-and in pieces of any even alignment, against one call on an aligned buffer."""
+"""Launches of short calls and short blocks: a segment whose blocks take one
+launch or several, its histograms in LDS or not; samples carried between calls
+from buffers and in pieces of any even alignment, against one call on an aligned
+buffer; the library's own count of blocks per launch against a stated one."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,8 @@ F0, BW = 326.5, 16.0
 
 @pytest.mark.parametrize("form", ["fp32", "mixed_valu"])
 @pytest.mark.parametrize("nsamp,nbins", [(4096, 1), (40_001, 63), (40_001, 64), (40_001, 65), (40_001, 8192),
-                                         (300_007, 129), (100, 64)])
+                                         (300_007, 129), (100, 64),
+                                         (8_000_011, 64)])
 def test_segment_launches(nsamp, nbins, form):
     import torch
     import paper_1503_01405_amd as P
@@ -62,3 +64,67 @@ def test_carried_samples(pieces):
         k += 1
     got, want = run(parts), run([x])
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+# the library's own count of short blocks per launch against 16: whole stream,
+# sub-integrations that launches cut (few and many bins), histograms in global
+# memory, a stream in pieces
+@pytest.mark.parametrize("form", ["fp32", "half", "mixed", "mixed_valu", "bf16"])
+@pytest.mark.parametrize("log2n,nbins,subint", [(10, 64, 0), (12, 64, 50_001), (14, 3000, 400_000), (16, 9000, 0),
+                                                (16, 9000, 700_001), (17, 128, 0)])
+def test_default_launches(log2n, nbins, subint, form):
+    import torch
+    import paper_1503_01405_amd as P
+    nsamp = 4_000_003
+    x = torch.from_numpy(synth.white_stream_int8(84, nsamp)).cuda()
+    outs = []
+    for batch, piece in ((16, nsamp), (0, nsamp), (0, 1_500_001)):
+        try:
+            plan = P.Plan(F0, BW, 0.005, 1 << log2n, nbins, 0.0123, precision=form, max_batch=batch,
+                          subint_nsamp=subint, decim=16)
+        except P.PondError:
+            pytest.skip("the form has no columns this short")
+        prof, ser = [], []
+        for at in range(0, nsamp, piece):
+            a, b = plan.process(x[2 * at:2 * min(at + piece, nsamp)])
+            prof.append(a.cpu().numpy())
+            ser.append(b.cpu().numpy())
+        prof.append(plan.flush().cpu().numpy())
+        plan.close()
+        outs.append((np.concatenate(prof), np.concatenate(ser)))
+    for got in outs[1:]:
+        assert np.array_equal(got[0], outs[0][0]) and np.array_equal(got[1], outs[0][1])
+
+
+@pytest.mark.parametrize("log2n", [11, 15, 18])
+@pytest.mark.parametrize("form", ["fp32", "mixed_valu"])
+def test_default_launches_of_real_input(log2n, form):
+    import torch
+    import paper_1503_01405_amd as P
+    nsamp = 4_000_002
+    x = torch.from_numpy(synth.white_stream_int8(85, nsamp)).cuda()
+    outs = []
+    for batch in (16, 0):
+        plan = P.Plan(F0, BW, 0.005, 1 << log2n, 100, 0.0123, precision=form, max_batch=batch, subint_nsamp=1_000_002,
+                      decim=32, sideband="lsb")
+        prof, ser = plan.process(x)
+        outs.append((np.concatenate([prof.cpu().numpy(), plan.flush().cpu().numpy()]), ser.cpu().numpy()))
+        plan.close()
+    assert np.array_equal(outs[1][0], outs[0][0]) and np.array_equal(outs[1][1], outs[0][1])
+
+
+@pytest.mark.parametrize("form", ["fp32", "half"])
+def test_default_launches_of_a_search(form):
+    import torch
+    import paper_1503_01405_amd as P
+    nsamp = 2_000_003
+    x = torch.from_numpy(synth.white_stream_int8(86, nsamp)).cuda()
+    dms, outs = [0.0, 0.01, 0.05, 0.2, 0.6], []
+    for batch in (16, None):
+        h = P.pond_search_create(F0, BW, dms, 100, 0.0123, 1 << 12, 1 << 18, P.FORMS[form], max_batch=batch)
+        prof = torch.empty(len(dms), 100, device="cuda")
+        assert P.pond_search_run(h, x, nsamp, prof) == P.POND_OK
+        torch.cuda.synchronize()
+        P.pond_search_destroy(h)
+        outs.append(prof.cpu().numpy())
+    assert np.array_equal(outs[1], outs[0])
