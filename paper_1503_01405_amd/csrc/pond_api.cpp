@@ -415,43 +415,25 @@ int64_t n_blocks_for(int64_t nsamp, int64_t nfft, int64_t hop) {
 
 namespace pond {
 
-namespace {
-// splitmix64 (Steele, Lea & Flood 2014): the calibration noise generator.
-uint64_t splitmix64(uint64_t x) {
-    x += 0x9e3779b97f4a7c15ull;
-    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
-    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
-    return x ^ (x >> 31);
-}
-}  // namespace
-
 hipError_t half_power_gain(const HalfCal& c, const std::function<hipError_t(int, const void**)>& middle,
                            double* gain) {
     const int log2n = c.log2n1 + c.log2n2;
     const int64_t n = (int64_t)1 << log2n;
     const int64_t nblk = n >= ((int64_t)1 << 22) ? 1 : ((int64_t)1 << 22) / n;
     const int64_t nsamp = nblk * n;
-    std::vector<int8_t> iq((size_t)(2 * nsamp));
-    int64_t energy = 0;
-    for (int64_t i = 0; i < nsamp; i += 4) {
-        const uint64_t h = splitmix64((uint64_t)i);
-        for (int k = 0; k < 8; ++k) {
-            const int8_t v = (int8_t)((h >> (8 * k)) & 0xff);
-            iq[(size_t)(2 * i + k)] = v;
-            energy += (int64_t)v * v;
-        }
-    }
-    int8_t* d_iq = nullptr;
-    float* d_ser = nullptr;
-    uint64_t* d_part = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&d_iq), iq.size());
     const int64_t nser = nsamp / 16;
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&d_ser), (size_t)nser * sizeof(float));
-    // per-workgroup partials of a one-bin fold (unused) and the status word
+    // One allocation: the noise, the series, the per-workgroup partials of a
+    // one-bin fold (unused) with the status word, the noise's energy.
     constexpr int64_t kParts = 4096;
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&d_part), (size_t)kParts * 12 + 8);
-    if (e == hipSuccess) e = hipMemcpy(d_iq, iq.data(), iq.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(d_part, 0, (size_t)kParts * 12 + 8);
+    char* buf = nullptr;
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&buf),
+                             (size_t)(2 * nsamp + nser * (int64_t)sizeof(float) + kParts * 12 + 16));
+    int8_t* d_iq = reinterpret_cast<int8_t*>(buf);
+    float* d_ser = reinterpret_cast<float*>(buf + 2 * nsamp);
+    uint64_t* d_part = reinterpret_cast<uint64_t*>(buf + 2 * nsamp + nser * (int64_t)sizeof(float));
+    uint64_t* d_energy = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(d_part) + kParts * 12 + 8);
+    if (e == hipSuccess) e = hipMemset(d_part, 0, (size_t)kParts * 12 + 16);
+    if (e == hipSuccess) e = launch_calibration_noise(reinterpret_cast<uint64_t*>(d_iq), nsamp / 4, d_energy, nullptr);
     for (int64_t b = 0; b < nblk && e == hipSuccess; b += c.max_batch) {
         const int nb = (int)(nblk - b < c.max_batch ? nblk - b : c.max_batch);
         K1Args a1{};
@@ -494,11 +476,11 @@ hipError_t half_power_gain(const HalfCal& c, const std::function<hipError_t(int,
         e = launch_k3(c.prec, c.log2n2, a3, grid, 12, nullptr);
     }
     std::vector<float> ser((size_t)nser);
+    uint64_t energy = 0;
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e == hipSuccess) e = hipMemcpy(ser.data(), d_ser, (size_t)nser * sizeof(float), hipMemcpyDeviceToHost);
-    if (d_iq) (void)hipFree(d_iq);
-    if (d_ser) (void)hipFree(d_ser);
-    if (d_part) (void)hipFree(d_part);
+    if (e == hipSuccess) e = hipMemcpy(&energy, d_energy, 8, hipMemcpyDeviceToHost);
+    if (buf) (void)hipFree(buf);
     if (e != hipSuccess) return e;
     double power = 0.0;
     for (float v : ser) power += (double)v;
@@ -731,7 +713,7 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
         cal.log2n2 = p->log2n2;
         cal.tw2 = p->tw2;
         cal.work = p->work;
-        cal.max_batch = p->max_batch;
+        cal.max_batch = std::max(p->max_batch, p->launch_batch);
         cal.f16_cols = 2 * p->hop == p->nfft;
         double g = 1.0;
         chk(half_power_gain(

@@ -205,6 +205,9 @@ hipError_t launch_copy_u128(void* dst, const void* src, int64_t n16, hipStream_t
 hipError_t launch_zero_u64(uint64_t* p, int64_t n, hipStream_t s);
 // n words of pseudo-random bits (splitmix64 of index and seed): timing input.
 hipError_t launch_fill_noise_u64(uint64_t* p, int64_t n, uint64_t seed, hipStream_t s);
+// The float16 calibration's noise, byte k of word w that of splitmix64(4 w), and
+// the sum of its squares added to *energy.
+hipError_t launch_calibration_noise(uint64_t* iq, int64_t words, uint64_t* energy, hipStream_t s);
 // w[t] = exp(-2 pi i t / n) for t < n, float64 sine/cosine rounded to float32.
 hipError_t launch_stage_twiddles(float2* w, int64_t n, hipStream_t s);
 // What a segment call prepares: row table (float4 or float2 as below), stage

@@ -128,3 +128,20 @@ def test_default_launches_of_a_search(form):
         P.pond_search_destroy(h)
         outs.append(prof.cpu().numpy())
     assert np.array_equal(outs[1], outs[0])
+
+
+# the float16 forms' power scale, measured at creation: mean powers are those of
+# the float32 form (float16 rounding of random sign; one part in a thousand)
+@pytest.mark.parametrize("form", ["half", "mixed"])
+@pytest.mark.parametrize("log2n", [12, 17, 22, 23])
+def test_power_scale(log2n, form):
+    import torch
+    import paper_1503_01405_amd as P
+    nsamp = 3 << log2n
+    x = torch.from_numpy(synth.white_stream_int8(87, nsamp)).cuda()
+    means = []
+    for f in ("fp32", form):
+        plan = P.Plan(F0, BW, 0.01, 1 << log2n, 64, 0.0123, precision=f, max_batch=0, decim=16)
+        means.append(plan.process(x)[1].double().mean().item())
+        plan.close()
+    assert abs(means[1] / means[0] - 1) < 1e-3
