@@ -300,14 +300,16 @@ static hipError_t k1_one(const K1Args& a, hipStream_t s) {
     if constexpr (CFORM == kFormF16 && LOG2N2 == 10) {
         // 32-column tiles where they leave a workgroup for every CU and every
         // block's samples are 4-byte aligned (blocks start at multiples of 16
-        // samples, the carried tail at a block; a call's input may start anywhere)
+        // samples, the carried tail at a block; a call's input may start anywhere),
+        // and no pair of columns lies half in the tail, half in the input
         const bool aligned = ((reinterpret_cast<uintptr_t>(a.in) - 2 * (uintptr_t)a.in_start) & 3) == 0 &&
                              ((reinterpret_cast<uintptr_t>(a.tail) - 2 * (uintptr_t)a.tail_start) & 3) == 0;
+        const bool split_pair = straddle && (a.in_start & 1);
         const int wide_tiles = tiles_per_block / 2;
         K1Args w = c;
         while (w.chain > 1 && (a.nblocks + w.chain - 1) / w.chain * wide_tiles < kWideTiles) --w.chain;
         const int wide_groups = (a.nblocks + w.chain - 1) / w.chain * wide_tiles;
-        if ((FORM == kFormF16 || mx16) && aligned && wide_groups >= kWideTiles) {
+        if ((FORM == kFormF16 || mx16) && aligned && !split_pair && wide_groups >= kWideTiles) {
             const int grid = (wide_groups + 7) & ~7;
             if (chained && w.chain > 1)
                 hipLaunchKernelGGL((k1_chain_colfft<LOG2N2, T, CFORM, false, true>), dim3(grid), dim3(1 << LOG2N2), 0,

@@ -64,3 +64,25 @@ def test_fold_edges(nbins, period, subint, decim, form):
         tol = 1e-6 if form == "fp32" else 1e-4 + 3 * eps / np.sqrt(m / nbins)
         assert np.linalg.norm(p - w) <= tol * np.linalg.norm(w)
     assert np.linalg.norm(ser - r["series"]) <= (1e-5 if form == "fp32" else 1e-2) * np.linalg.norm(r["series"])
+
+
+# a call whose first sample is an odd one of the stream, on a buffer that keeps the
+# stream's alignment: a pair of columns lies half in the carried tail, half in the
+# call's input
+@pytest.mark.parametrize("form", ["half", "mixed"])
+@pytest.mark.parametrize("first", [3_000_001, 3_000_002, N + 1, 2 * N - 1])
+def test_odd_carry(first, form):
+    import torch
+    import paper_1503_01405_amd as P
+    nsamp = 12_000_003
+    x = torch.from_numpy(synth.white_stream_int8(72, nsamp)).cuda()
+    want = gpu(x, 6.007, form, 16, 128, 0.0123)
+    plan = P.Plan(F0, BW, 6.007, N, 128, 0.0123, precision=form, max_batch=16, subint_nsamp=0, decim=16)
+    # fill the other carry with samples of its own first
+    plan.process(torch.full((2 * (first + 1),), 77, dtype=torch.int8, device="cuda"))
+    plan.flush()
+    ser = [plan.process(y)[1].cpu().numpy() for y in (x[:2 * first], x[2 * first:2 * first + 2 * 5_000_001],
+                                                      x[2 * first + 2 * 5_000_001:])]
+    prof = plan.flush().cpu().numpy()
+    plan.close()
+    assert np.array_equal(np.concatenate(ser), want[1]) and np.array_equal(prof, want[0])
