@@ -145,3 +145,24 @@ def test_power_scale(log2n, form):
         means.append(plan.process(x)[1].double().mean().item())
         plan.close()
     assert abs(means[1] / means[0] - 1) < 1e-3
+
+
+# calls whose blocks are no multiple of a launch: one launch of up to twice the
+# cached count, several of about the same size
+@pytest.mark.parametrize("form,log2n", [("fp32", 22), ("half", 23)])
+@pytest.mark.parametrize("nblocks", [1, 4, 5, 7, 9])
+def test_uneven_launches(nblocks, form, log2n):
+    import torch
+    import paper_1503_01405_amd as P
+    n = 1 << log2n
+    nsamp = n + (nblocks - 1) * (n // 2)
+    dm = 20.0 * n / (1 << 22)
+    x = torch.from_numpy(synth.white_stream_int8(88, nsamp)).cuda()
+    outs = []
+    for batch in (1, 0):
+        plan = P.Plan(F0, BW, dm, n, 100, 0.0123, precision=form, max_batch=batch, subint_nsamp=0, decim=16)
+        ser = plan.process(x)[1].cpu().numpy()
+        outs.append((plan.flush().cpu().numpy(), ser))
+        plan.close()
+    assert outs[0][1].size == nblocks * (n // 2) // 16
+    assert np.array_equal(outs[1][0], outs[0][0]) and np.array_equal(outs[1][1], outs[0][1])
