@@ -406,11 +406,12 @@ int cached_batch(int64_t nfft, int32_t precision, int32_t kind, int max_batch) {
 }
 
 // Blocks of the next launch of `left`: no short launch at the end.  Less than two
-// launches' worth goes at once where the work area (room blocks) holds it, more in
-// launches of about the same size (float32, 2^22, calls of 5 blocks in
-// launches of 4: 1,110 us as 4 and 1, 1,047 at once).
+// launches' worth goes at once where the work area (room blocks) holds it, else in
+// equal parts (float32, 2^22, calls of 5 blocks in launches of 4: 1,110 us as 4
+// and 1, 1,047 at once).
 int64_t launch_blocks(int64_t left, int64_t batch, int64_t room) {
-    const int64_t launches = std::max(std::max<int64_t>(left / batch, 1), (left + room - 1) / room);
+    if (left >= 2 * batch) return batch;
+    const int64_t launches = (left + room - 1) / room;
     return (left + launches - 1) / launches;
 }
 
