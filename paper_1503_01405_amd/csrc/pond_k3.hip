@@ -372,12 +372,16 @@ k3_colinv_detect_fold(K3Args args) {
                     bb = fold_bin(f0i + hi, fnf, a.inv_pfs, a.nbins, &tb2);
                 }
                 if (ba == bin0 && ta == fl && bb == bin15 && tb2 == t15) {
-                    float sa = 0.f;
+                    // (each from its own samples: the rest of s16 carries the
+                    // rounding of both, either sign where the second is silent)
+                    float sa = 0.f, sb = 0.f;
 #pragma unroll
                     for (int i = 0; i < G; ++i) sa += i < hi ? (REAL ? pr[i] : p[i]) : 0.f;
-                    const uint64_t fa = fold_fixed(sa);
-                    k3_fold_add(a, hsum, hcnt, sub0, bin0, fa, (uint32_t)hi);
-                    k3_fold_add(a, hsum, hcnt, sub0, bin15, fx - fa, (uint32_t)(G - hi));
+                    const int hi2 = (int)opaque((uint32_t)hi);  // (16 comparisons made again, not kept)
+#pragma unroll
+                    for (int i = 0; i < G; ++i) sb += i < hi2 ? 0.f : (REAL ? pr[i] : p[i]);
+                    k3_fold_add(a, hsum, hcnt, sub0, bin0, fold_fixed(sa), (uint32_t)hi);
+                    k3_fold_add(a, hsum, hcnt, sub0, bin15, fold_fixed(sb), (uint32_t)(G - hi));
                     continue;
                 }
             }
