@@ -323,7 +323,8 @@ k3_colinv_detect_fold(K3Args args) {
                 }
             }
             if (!isfinite(s16)) flags |= 1u;
-            if (!(s16 < (float)kFoldRangeLimit)) flags |= 2u;
+            // (the limit is on what is added at once, not on the group)
+            auto range = [&](float v) { return v < (float)kFoldRangeLimit ? 0u : 2u; };
 
             // Fold: one contribution when all outputs of the group share pulse,
             // bin and sub-integration.  (The element indices are exact in
@@ -345,6 +346,7 @@ k3_colinv_detect_fold(K3Args args) {
                 one_sub = d0 - sub0 * a.subint + 15 < a.subint;
             }
             if (one_sub && y0 + fma(x0, a.fold_safe1, a.fold_safe0) < next) {
+                flags |= range(s16);
                 k3_fold_add(a, hsum, hcnt, sub0, bin0, fx, G);
                 continue;
             }
@@ -353,6 +355,7 @@ k3_colinv_detect_fold(K3Args args) {
             double t15;
             const int bin15 = fold_bin(f0i + G - 1, fnf, a.inv_pfs, a.nbins, &t15);
             if (one_sub && bin0 == bin15 && fl == t15) {
+                flags |= range(s16);
                 k3_fold_add(a, hsum, hcnt, sub0, bin0, fx, G);
                 continue;
             }
@@ -380,6 +383,7 @@ k3_colinv_detect_fold(K3Args args) {
                     const int hi2 = (int)opaque((uint32_t)hi);  // (16 comparisons made again, not kept)
 #pragma unroll
                     for (int i = 0; i < G; ++i) sb += i < hi2 ? 0.f : (REAL ? pr[i] : p[i]);
+                    flags |= range(sa) | range(sb);
                     k3_fold_add(a, hsum, hcnt, sub0, bin0, fold_fixed(sa), (uint32_t)hi);
                     k3_fold_add(a, hsum, hcnt, sub0, bin15, fold_fixed(sb), (uint32_t)(G - hi));
                     continue;
@@ -395,6 +399,7 @@ k3_colinv_detect_fold(K3Args args) {
                 double ti;
                 const int bi = fold_bin(f0i + i, fnf, a.inv_pfs, a.nbins, &ti);
                 const int si = a.subint > 0 ? (int)subint_rel(d0 + ci, a.subint, a.inv_subint) : 0;
+                flags |= range(pi);
                 k3_fold_add(a, hsum, hcnt, si, bi, fold_fixed(pi), 1);
             }
         }

@@ -119,3 +119,34 @@ def test_overflow_stays_on_its_side_of_the_edge(side):
     want = np.bincount(bins[cells], sums, nbins) / count
     groups = np.bincount(bins[cells], minlength=nbins) / count
     assert (np.abs(prof - want) <= 16 * 2.0 ** -24 * want + UNIT * groups).all()
+
+
+# the range flag is of one contribution, the powers of a group that share a bin: a
+# peak of 1.5e12 (2^40: 1.1e12) over two samples in different bins does not set it,
+# on one sample it does
+@pytest.mark.parametrize("where", ["two bins", "many bins", "one sample"])
+def test_range_flag_of_contributions(where):
+    import torch
+    import paper_1503_01405_amd as P
+    n = 1 << 26
+    dm = 0.9 * n / 61_100
+    nbins, per_bin = (64, 5.3) if where == "many bins" else (1024, 13_107.37)
+    print("case: range flag,", where, flush=True)
+    plan = P.Plan(F0, BW, dm, n, nbins, nbins * per_bin / FS, precision="fp32", max_batch=1, subint_nsamp=0, decim=16)
+    try:
+        info = plan.info()
+        n_front, hop = info["n_front"], info["hop"]
+        q = int((n_front + hop / 2) / per_bin)
+        while True:
+            at = int(np.ceil(q * per_bin)) - n_front  # an edge's first sample
+            if at % 16 == 8:
+                break
+            q += 1
+        peak = float(at) if where == "one sample" else at - 0.5
+        _, ser = plan.process(matched(n, dm, peak + n_front))
+        ser = ser.cpu().numpy()
+        status = plan.info()["status"]
+    finally:
+        plan.close()
+    assert ser.argmax() == at // 16 and ser.max() > 2.0 ** 40 and np.sort(ser)[-2] < 2.0 ** 39
+    assert status == (P.POND_STATUS_RANGE if where == "one sample" else 0)
