@@ -71,13 +71,14 @@ __device__ __forceinline__ void k3_fold_add(K3Kernarg& a, uint64_t* hsum, uint32
 // every tile in L2, 12.2 without the series, whose 4-byte stores fall in one
 // cache line each).  So the powers take no LDS of their own (68 KB instead of
 // 133) and the epilogue's scalars and float64 constants no registers (k3_kernarg,
-// K3Args), which lets two workgroups share a CU in packed float16 (TWO) and
-// float32 fetch its next tile; the fold phase of a group is one float64 product
-// and the second one only near a bin's edge.  2^23, per block in launches of 4 /
-// 16: packed float16 14.4 / 15.4 -> 12.9 / 14.4 us; float32 24.5 -> 24.0 at 8.
+// K3Args), which lets two workgroups share a CU in packed float16 (TWO); the fold
+// phase of a group is one float64 product and the second one only near a bin's
+// edge.  2^23, per block, before and now: packed float16 in launches of 4 / 8
+// 13.5 / 14.3 and 12.1 / 13.1 us; float32 in launches of 3 / 8 18.8 / 22.7 and
+// 18.4 / 22.5.
 // WIDE (matrix-core form): tiles of 32 columns, two adjacent ones per thread,
-// one workgroup per CU (it needs more than 64 registers): 15.9 -> 15.4; packed
-// float16 gains nothing from it (14.5 at 16 blocks, 16.4 at 4).  A reduction of
+// one workgroup per CU (it needs more than 64 registers): 14.2 / 15.3 and 13.7 /
+// 13.9 in launches of 4 / 8; packed float16 gains nothing from it.  A reduction of
 // the powers across lanes in place of the LDS buffer (four DPP steps) cost 25%
 // more VALU instructions and 8% more time.
 template <int LOG2N2, class T, int FORM, bool REAL, bool TWO, bool WIDE>
@@ -131,10 +132,15 @@ k3_colinv_detect_fold(K3Args args) {
 
     // The column tile of an item, as stored.  Where one workgroup has the CU
     // (TWO: two share it and hide each other's loads), the next item's tile
-    // is loaded while this one is transformed and folded.  WIDE: a thread's two
+    // is loaded while this one is transformed and folded, if it is 64 bytes a
+    // thread: the 128 of float32 and of WIDE cost more than they hide where the
+    // launch's work area is cached (2^23, per block in launches of 1 / 3 / 8:
+    // float32 28.9 / 19.5 / 21.8 us with the read-ahead, 24.7 / 18.4 / 22.5
+    // without; matrix-core form of 1 / 4 / 8: 19.7 / 15.0 / 14.6 and 19.1 / 13.7 /
+    // 13.9).  WIDE: a thread's two
     // columns are one 8-byte access (4-byte aligned), but for the pair that
     // crosses n1 (r0 odd), whose second column is column 0.
-    constexpr bool kPrefetch = !TWO && LOG2N2 >= 9 && (sizeof(T) == 4 || (LOG2N2 == 10 && !REAL));
+    constexpr bool kPrefetch = !TWO && !WIDE && LOG2N2 >= 9 && sizeof(T) == 4;
     using Raw = std::conditional_t<WIDE, hh2, std::conditional_t<H16, h2, T>>;
     auto load_tile = [&](int it, Raw(&dst)[16]) {
         const int bb = it >> log2tiles;
@@ -435,9 +441,8 @@ static hipError_t k3_launch(const K3Args& a, int grid, size_t dyn, hipStream_t s
     return hipGetLastError();
 }
 
-// 32-column tiles (items: of 16 columns): the float16-arithmetic forms' columns
-// of 2^10, where they leave an item for every CU and the histogram fits beside
-// them.
+// 32-column tiles (items: of 16 columns): the matrix-core form's columns of 2^10,
+// where they leave an item for every CU and the histogram fits beside them.
 constexpr int64_t kWideItems = 256;
 static bool k3_wide(bool mfma, int log2n2, int64_t items, size_t dyn) {
     return mfma && log2n2 == 10 && items / 2 >= kWideItems && K3Shape<10>::LDS_WIDE + dyn <= kLdsBytes;
