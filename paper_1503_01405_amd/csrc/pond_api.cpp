@@ -1062,23 +1062,44 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     const float k3_scale = 1.0f;
 
     int64_t b = p->blocks_done;
+    // Blocks of the launch that begins with block `at`.  Sub-integrations bound it:
+    // as many blocks as touch no more of them than the histogram in LDS holds (one
+    // block, or a single sub-integration beyond it: any number, in global memory).
+    // `many` (more than max_batch blocks): no more entries of several
+    // sub-integrations than leave K3 its workgroups per CU, unless max_batch blocks
+    // with all of the LDS are more.
+    auto blocks_at = [&](int64_t at, bool many) -> int64_t {
+        const int64_t left = nb_total - at;
+        const int64_t want = many ? launch_blocks(left, p->launch_batch, p->launch_batch)
+                                  : launch_blocks(left, std::min(p->launch_batch, p->max_batch), p->max_batch);
+        if (subint <= 0 || nbins > p->hist_cap) return want;
+        const int64_t s0 = at * hop / subint;
+        auto within = [&](int64_t blocks, int64_t cap) {
+            const int64_t room = cap / nbins;
+            if (((at + blocks) * hop - 1) / subint - s0 < room) return blocks;
+            return std::max<int64_t>(1, (s0 + room) * subint / hop - at);
+        };
+        int64_t fit = within(std::min<int64_t>(want, p->max_batch), p->hist_cap);
+        if (many) fit = std::max(fit, within(want, std::min(p->hist_cap, std::max<int64_t>(nbins, kFullBins))));
+        return fit < want ? launch_blocks(left, fit, fit) : want;
+    };
+    // Larger launches only where they are fewer (47 blocks of 2^20, sub-integrations
+    // of 1.5 blocks: 24, 12 and 11 blocks 379 us, 16, 16 and 15 of them 357).
+    bool many = p->launch_batch > p->max_batch;
+    if (many && subint > 0 && nbins <= p->hist_cap) {
+        auto launches = [&](bool m) {
+            int64_t k = 0;
+            for (int64_t at = b; at < nb_total; at += blocks_at(at, m)) ++k;
+            return k;
+        };
+        many = launches(true) < launches(false);
+    }
     ReduceQueue rq;
     int64_t rq_blocks = 0;  // blocks whose fold partials are queued
     while (b < nb_total) {
-        int64_t nb = launch_blocks(nb_total - b, p->launch_batch, std::max(p->launch_batch, p->max_batch));
-        int64_t s_lo = 0, nsub = 1;
-        for (;;) {
-            if (subint > 0) {
-                s_lo = (b * hop) / subint;
-                const int64_t s_hi = ((b + nb) * hop - 1) / subint;
-                nsub = s_hi - s_lo + 1;
-            }
-            // beyond max_batch no more bins of several sub-integrations than leave
-            // K3 its workgroups per CU; in global memory any number
-            const int64_t cap = nb > p->max_batch ? std::min(p->hist_cap, std::max<int64_t>(nbins, kFullBins)) : p->hist_cap;
-            if (nbins > p->hist_cap || nsub * nbins <= cap || nb == 1) break;
-            nb = (nb + 1) / 2;
-        }
+        const int64_t nb = blocks_at(b, many);
+        const int64_t s_lo = subint > 0 ? b * hop / subint : 0;
+        const int64_t nsub = subint > 0 ? ((b + nb) * hop - 1) / subint - s_lo + 1 : 1;
         const int64_t entries = nsub * nbins;
         const bool global_mode = entries > p->hist_cap;
 
