@@ -77,6 +77,7 @@ struct pond_plan {
     int32_t nbins = 0, precision = 0;
     int max_batch = 1;
     int launch_batch = 1;       // blocks per launch of a call
+    bool given = false;         // max_batch stated by the caller or tuned: launched as it is
     size_t elem = 8;
     // Real two-channel input (Sec. 3.1: channels A and B added in phase):
     // element m packs real samples 2m, 2m+1; every count above is in
@@ -405,10 +406,11 @@ int cached_batch(int64_t nfft, int32_t precision, int32_t kind, int max_batch) {
     return (int)std::min<int64_t>(max_batch, std::max<int64_t>(3, fit));
 }
 
-// Blocks of the next launch of `left`: no short launch at the end.  Less than two
-// launches' worth goes at once where the work area (room blocks) holds it, else in
-// equal parts (float32, 2^22, calls of 5 blocks in launches of 4: 1,110 us as 4
-// and 1, 1,047 at once).
+// Blocks of the next launch of `left` where the library chooses (a stated or tuned
+// count is launched as it is): no short launch at the end.  Less than two launches'
+// worth goes at once where the work area (room blocks) holds it, else in equal parts
+// (float32, 2^22, calls of 5 blocks in launches of 4: 1,110 us as 4 and 1, 1,047 at
+// once).
 int64_t launch_blocks(int64_t left, int64_t batch, int64_t room) {
     if (left >= 2 * batch) return batch;
     const int64_t launches = (left + room - 1) / room;
@@ -645,7 +647,7 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     p->elem = precision == POND_FP32 ? 8 : 4;
     const bool autotune = max_batch == POND_BATCH_AUTOTUNE;
     // (acc_slots: the server's plans, whose max_batch is what its budget left)
-    const bool chosen = acc_slots == 0 && (max_batch > 0 || (autotune && kind == POND_INPUT_COMPLEX));
+    p->given = acc_slots == 0 && (max_batch > 0 || (autotune && kind == POND_INPUT_COMPLEX));
     p->max_batch = max_batch = default_max_batch(nfft, precision, max_batch);
 
     p->hist_cap = hist_capacity(p->log2n2, p->precision);
@@ -703,7 +705,7 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     chk(hipMalloc(reinterpret_cast<void**>(&p->part_cnt), (size_t)kPartEntries * 4));
     chk(hipMalloc(reinterpret_cast<void**>(&p->status), 8));
     if (e == hipSuccess && autotune && kind == POND_INPUT_COMPLEX) chk(tune_plan(p));
-    p->launch_batch = chosen ? p->max_batch : cached_batch(nfft, precision, kind, p->max_batch);
+    p->launch_batch = p->given ? p->max_batch : cached_batch(nfft, precision, kind, p->max_batch);
     // (a server's plan is charged for max_batch blocks)
     if (acc_slots > 0) p->launch_batch = std::min(p->launch_batch, p->max_batch);
     if (p->launch_batch > p->max_batch && e == hipSuccess &&
@@ -1070,8 +1072,9 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     // with all of the LDS are more.
     auto blocks_at = [&](int64_t at, bool many) -> int64_t {
         const int64_t left = nb_total - at;
-        const int64_t want = many ? launch_blocks(left, p->launch_batch, p->launch_batch)
-                                  : launch_blocks(left, std::min(p->launch_batch, p->max_batch), p->max_batch);
+        const int64_t want = p->given ? std::min<int64_t>(left, p->max_batch)
+                             : many   ? launch_blocks(left, p->launch_batch, p->launch_batch)
+                                      : launch_blocks(left, std::min(p->launch_batch, p->max_batch), p->max_batch);
         if (subint <= 0 || nbins > p->hist_cap) return want;
         const int64_t s0 = at * hop / subint;
         auto within = [&](int64_t blocks, int64_t cap) {
