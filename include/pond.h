@@ -35,8 +35,9 @@
  *     null stream) and never synchronise it; all counts are derived on the
  *     host from the plan's own state.  Device pointers must stay valid, and
  *     iq unmodified, until the stream has passed the call.
- *   - A plan owns its device workspace (allocated in create, freed in
- *     destroy) and its stream state.  A plan is not thread-safe; distinct
+ *   - A plan owns its device workspace (allocated in create, enlarged by
+ *     the first call that needs more unless its stream is being captured,
+ *     freed in destroy) and its stream state.  A plan is not thread-safe; distinct
  *     plans are independent.  Successive calls on one plan must be ordered
  *     on the device: use one stream per plan, or order the streams.  The
  *     plan is bound to the device that is current when it is created.
@@ -196,9 +197,9 @@ pond_plan* pond_plan_create(double f0_mhz, double bw_mhz, double dm,
  * plus the default) during creation and
  * keep the fastest per block, a larger launch winning only by more than 0.5%;
  * other values <= 0 pick the default (2^29 bytes of work area, 1 .. 16
- * blocks; the calls then launch more of the shorter blocks at once, up to 2^27
- * bytes of work area if the device has them, and fewer of the longer ones where
- * that keeps the work area cached).  With the environment variable POND_AUTOTUNE_CACHE naming a
+ * blocks; calls with more of the shorter blocks enlarge the work area, up to 2^27
+ * bytes if the device has them, and launch them at once; longer blocks go fewer at
+ * a time where that keeps the work area cached).  With the environment variable POND_AUTOTUNE_CACHE naming a
  * text file, a choice already measured for the same device, nfft, form,
  * input kind and histogram placement is read from it instead, and new
  * choices are appended (one line each; the last matching line wins).
@@ -398,8 +399,8 @@ pond_search* pond_search_create(double f0_mhz, double bw_mhz, const double* dms,
  * max_batch > 0 as given; POND_BATCH_AUTOTUNE tunes each group as
  * pond_plan_create_ex does (its forward pass and two trials' inverse
  * passes timed on pseudo-random input; POND_AUTOTUNE_CACHE as there);
- * other values <= 0 the default (2^28 bytes of spectrum, 1 .. 16 blocks, or
- * more of the shorter ones up to 2^26 bytes, if the device has them).
+ * other values <= 0 the default (2^28 bytes of spectrum, 1 .. 16 blocks; runs on
+ * more of the shorter ones enlarge that, up to 2^26 bytes if the device has them).
  */
 pond_search* pond_search_create_ex(double f0_mhz, double bw_mhz, const double* dms, int32_t ntrials,
                                    int32_t nbins, double period_s, int64_t nfft_min, int64_t nfft_max,

@@ -76,7 +76,8 @@ struct pond_plan {
     int log2n = 0, log2n1 = 0, log2n2 = 0, hbits = 0;
     int32_t nbins = 0, precision = 0;
     int max_batch = 1;
-    int launch_batch = 1;       // blocks per launch of a call
+    int launch_batch = 1;       // blocks per launch of a call; more than max_batch once
+                                // the work area holds them
     bool given = false;         // max_batch stated by the caller or tuned: launched as it is
     size_t elem = 8;
     // Real two-channel input (Sec. 3.1: channels A and B added in phase):
@@ -93,7 +94,7 @@ struct pond_plan {
     float2* real_b = nullptr;
     float4* rtab = nullptr;     // [nfft + 1]
 
-    void* work = nullptr;
+    WorkArea work;
     int8_t* tail[2] = {nullptr, nullptr};
     int tcur = 0;
     int64_t tail_start = 0;
@@ -202,9 +203,10 @@ void free_plan_memory(pond_plan* p) {
     p->marks.clear();
     for (hipEvent_t e : p->event_pool) (void)hipEventDestroy(e);
     p->event_pool.clear();
-    void* ptrs[] = {p->work,   p->tail[0], p->tail[1], p->tw1,     p->tw2,         p->table,
-                    p->htable, p->tw4,     p->real_ad, p->real_b, p->rtab, p->tw_ck,       p->tw_hi,
-                    p->tw_lo,  p->acc_sum, p->acc_cnt, p->part_sum, p->part_cnt, p->status, p->chirp_split};
+    p->work.release();
+    void* ptrs[] = {p->tail[0], p->tail[1], p->tw1,    p->tw2,     p->table,   p->htable,  p->tw4,      p->real_ad,
+                    p->real_b,  p->rtab,    p->tw_ck,  p->tw_hi,   p->tw_lo,   p->acc_sum, p->acc_cnt,  p->part_sum,
+                    p->part_cnt, p->status, p->chirp_split};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
 }
@@ -426,6 +428,58 @@ int64_t n_blocks_for(int64_t nsamp, int64_t nfft, int64_t hop) {
 }  // namespace
 
 namespace pond {
+
+hipError_t WorkArea::create(int64_t usual, int64_t most, size_t bytes) {
+    block_bytes = bytes;
+    blocks = usual;
+    if (most > usual) blocks = (size_t)usual * bytes >= kLargeArea ? most : std::max<int64_t>(usual, kSmallArea / bytes);
+    hipError_t e = hipMalloc(&ptr, (size_t)blocks * bytes);
+    if (e != hipSuccess && blocks > usual) {
+        (void)hipGetLastError();
+        full = true;
+        blocks = usual;
+        e = hipMalloc(&ptr, (size_t)blocks * bytes);
+    }
+    if (e != hipSuccess) {
+        ptr = nullptr;
+        blocks = 0;
+    }
+    return e;
+}
+
+void WorkArea::grow(int64_t want, int64_t most, hipStream_t stream) {
+    if (full || want <= blocks || blocks >= most) return;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    int64_t n = blocks;
+    while (n < want) n *= 2;
+    n = std::min(n, most);
+    // (another thread may be capturing a stream of its own)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    void* q = nullptr;
+    const hipError_t e = hipMalloc(&q, (size_t)n * block_bytes);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        full = true;
+        return;
+    }
+    old.push_back(ptr);
+    ptr = q;
+    blocks = n;
+}
+
+void WorkArea::release() {
+    for (void* q : old) (void)hipFree(q);
+    old.clear();
+    if (ptr) (void)hipFree(ptr);
+    ptr = nullptr;
+    blocks = 0;
+}
 
 hipError_t half_power_gain(const HalfCal& c, const std::function<hipError_t(int, const void**)>& middle,
                            double* gain) {
@@ -708,13 +762,7 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     p->launch_batch = p->given ? p->max_batch : cached_batch(nfft, precision, kind, p->max_batch);
     // (a server's plan is charged for max_batch blocks)
     if (acc_slots > 0) p->launch_batch = std::min(p->launch_batch, p->max_batch);
-    if (p->launch_batch > p->max_batch && e == hipSuccess &&
-        hipMalloc(&p->work, (size_t)p->launch_batch * (size_t)nfft * p->elem) != hipSuccess) {
-        (void)hipGetLastError();
-        p->work = nullptr;
-        p->launch_batch = p->max_batch;  // no room for more
-    }
-    if (!p->work) chk(hipMalloc(&p->work, (size_t)p->max_batch * (size_t)nfft * p->elem));
+    if (e == hipSuccess) chk(p->work.create(p->max_batch, p->launch_batch, (size_t)nfft * p->elem));
     // Float16 arithmetic (packed float16 and matrix-core forms): the power
     // scale is 256 over the measured gain of the plan's float16 arithmetic
     // (the unit-taper table just built).
@@ -724,15 +772,15 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
         cal.log2n1 = p->log2n1;
         cal.log2n2 = p->log2n2;
         cal.tw2 = p->tw2;
-        cal.work = p->work;
-        cal.max_batch = std::max(p->max_batch, p->launch_batch);
+        cal.work = p->work.ptr;
+        cal.max_batch = (int)p->work.blocks;
         cal.f16_cols = 2 * p->hop == p->nfft;
         double g = 1.0;
         chk(half_power_gain(
             cal,
             [&](int nb, const void** res) {
-                *res = p->work;
-                return run_middle(p, p->work, nb, nullptr);
+                *res = p->work.ptr;
+                return run_middle(p, p->work.ptr, nb, nullptr);
             },
             &g));
         p->half_gain = g;
@@ -1064,6 +1112,10 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     const float k3_scale = 1.0f;
 
     int64_t b = p->blocks_done;
+    // More short blocks than the work area holds: a larger one, of as many as the
+    // call has up to launch_batch.
+    if (p->launch_batch > p->work.blocks) p->work.grow(nb_total - b, p->launch_batch, stream);
+    const int64_t batch = std::min<int64_t>(p->launch_batch, p->work.blocks);
     // Blocks of the launch that begins with block `at`.  Sub-integrations bound it:
     // as many blocks as touch no more of them than the histogram in LDS holds (one
     // block, or a single sub-integration beyond it: any number, in global memory).
@@ -1073,8 +1125,8 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     auto blocks_at = [&](int64_t at, bool many) -> int64_t {
         const int64_t left = nb_total - at;
         const int64_t want = p->given ? std::min<int64_t>(left, p->max_batch)
-                             : many   ? launch_blocks(left, p->launch_batch, p->launch_batch)
-                                      : launch_blocks(left, std::min(p->launch_batch, p->max_batch), p->max_batch);
+                             : many   ? launch_blocks(left, batch, batch)
+                                      : launch_blocks(left, std::min<int64_t>(batch, p->max_batch), p->max_batch);
         if (subint <= 0 || nbins > p->hist_cap) return want;
         const int64_t s0 = at * hop / subint;
         auto within = [&](int64_t blocks, int64_t cap) {
@@ -1088,7 +1140,7 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     };
     // Larger launches only where they are fewer (47 blocks of 2^20, sub-integrations
     // of 1.5 blocks: 24, 12 and 11 blocks 379 us, 16, 16 and 15 of them 357).
-    bool many = p->launch_batch > p->max_batch;
+    bool many = batch > p->max_batch;
     if (many && subint > 0 && nbins <= p->hist_cap) {
         auto launches = [&](bool m) {
             int64_t k = 0;
@@ -1115,7 +1167,7 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
         a1.block0 = b;
         a1.nblocks = (int32_t)nb;
         a1.log2n1 = p->log2n1;
-        a1.work = p->work;
+        a1.work = p->work.ptr;
         a1.tw2 = p->tw2;
         a1.scale = k1_scale;
         a1.f16_cols = 2 * hop == p->nfft;
@@ -1127,13 +1179,13 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
 
         if (real && p->real_three) {
             K2Args a2{};
-            a2.work = p->work;
+            a2.work = p->work.ptr;
             a2.nblocks = (int32_t)nb;
             a2.log2n2 = n2log;
             a2.tw1 = p->tw1;
             a2.tw4 = p->tw4;
             a2.scale = std::ldexp(1.0f, -p->log2n1);
-            RealSplitArgs rs{p->work, (int32_t)nb, p->log2n1, n2log, p->rtab};
+            RealSplitArgs rs{p->work.ptr, (int32_t)nb, p->log2n1, n2log, p->rtab};
             e = timed(1, nb, [&] {
                 hipError_t r = launch_k2(p->precision, kRowFwd, p->log2n1, a2, stream);
                 if (r == hipSuccess) r = launch_real_split(rs, stream);
@@ -1143,15 +1195,15 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
                 return r;
             });
         } else if (real) {
-            RealPairArgs rp{p->work, (int32_t)nb, n2log, p->tw1, p->tw4, p->real_ad, p->real_b};
+            RealPairArgs rp{p->work.ptr, (int32_t)nb, n2log, p->tw1, p->tw4, p->real_ad, p->real_b};
             e = timed(1, nb, [&] { return launch_real_pair(p->precision, p->log2n1, rp, stream); });
         } else {
-            e = timed(1, nb, [&] { return run_middle(p, p->work, (int)nb, stream); });
+            e = timed(1, nb, [&] { return run_middle(p, p->work.ptr, (int)nb, stream); });
         }
         if (e != hipSuccess) return fail(e);
 
         K3Args a3;
-        a3.work = p->work;
+        a3.work = p->work.ptr;
         a3.nblocks = (int32_t)nb;
         a3.log2n1 = p->log2n1;
         a3.hop = hop;

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include <functional>
+#include <vector>
 
 struct pond_plan;
 
@@ -297,6 +298,29 @@ int k3_grid(int log2n2, int prec, size_t dyn_lds, int64_t items, int64_t entries
 constexpr int64_t kHistCapMax = 8192;      // fold histogram entries held in LDS
 constexpr size_t kLdsBytes = 160 * 1024;   // gfx950 LDS per workgroup
 int64_t hist_capacity(int log2n2, int prec);
+
+// Blocks between the passes of a launch, or a search group's two areas of them.  The
+// library launches up to `most` short blocks at once; what that takes (2^27 bytes) is
+// there from the start where the usual count alone takes kLargeArea.  Plans of
+// shorter blocks start with kSmallArea, and the first call of more blocks grows it:
+// beyond 64 MB an allocation takes 27-60 us and its release 230, so that with 2^27
+// bytes each a plan of 2^14 points took 89 us to create and 270 to destroy, more than
+// its calls (now 65 and 49), and many small plans held 128 MB each.  The smaller
+// areas stay until the end: work queued before, or a captured graph, may still use
+// them (together they are less than the last one).
+struct WorkArea {
+    void* ptr = nullptr;
+    int64_t blocks = 0;
+    size_t block_bytes = 0;
+    bool full = false;          // the device had no room for more
+    std::vector<void*> old;
+    static constexpr size_t kLargeArea = (size_t)1 << 25, kSmallArea = (size_t)1 << 24;
+    hipError_t create(int64_t usual, int64_t most, size_t bytes);
+    // Room for min(want, most) blocks, if it can be had: not while the stream is
+    // captured (the graph would own the memory), and not if the device has none.
+    void grow(int64_t want, int64_t most, hipStream_t stream);
+    void release();
+};
 
 // Device bytes pond_plan_create_ex allocates for these arguments (with an
 // accumulator ring of acc_slots sub-integrations, at least 4), and the

@@ -32,6 +32,7 @@ struct Group {
     int64_t nfft = 0, hop = 0;
     int log2n = 0, log2n1 = 0, log2n2 = 0;
     int max_batch = 1;
+    int most_batch = 1;       // blocks per launch; more than max_batch once the area holds them
     float pscale = 1.0f;  // detected-power scale of K3 (packed float16: see pond_api.cpp)
     std::vector<int> trials;
     float2* tw1 = nullptr;    // exp(-2 pi i t / n1)
@@ -39,8 +40,9 @@ struct Group {
     float2* tw4 = nullptr;    // [n2][n1] four-step twiddle
     void* htw4 = nullptr;     // packed float16 form: [n2][n1] twiddle / 16
     double* geo = nullptr;    // [n2][n1] chirp turns per unit DM, shared by the group's trials
-    void* spec = nullptr;     // max_batch blocks of spectrum
-    void* out = nullptr;      // max_batch blocks of one trial's row-inverse output
+    WorkArea area;            // spectrum of its blocks, then one trial's row-inverse output of as many
+    void* spec() const { return area.ptr; }
+    void* out(size_t elem) const { return static_cast<char*>(area.ptr) + (size_t)area.blocks * nfft * elem; }
     bool tuned = false;       // max_batch chosen by the autotuner
     TuneResult tune;
 };
@@ -75,7 +77,8 @@ namespace {
 
 void free_search(pond_search* s) {
     for (auto& g : s->groups) {
-        void* ptrs[] = {g.tw1, g.tw2, g.tw4, g.htw4, g.geo, g.spec, g.out};
+        g.area.release();
+        void* ptrs[] = {g.tw1, g.tw2, g.tw4, g.htw4, g.geo};
         for (void* q : ptrs)
             if (q) (void)hipFree(q);
     }
@@ -357,20 +360,8 @@ pond_search* pond_search_create_ex(double f0_mhz, double bw_mhz, const double* d
         // 499 (1,024; the rule 4,096), 2^14 2,977 and 373, 2^16 948 and 337, 2^18
         // 443 and 354; float32 2^16 1,078 and 382.
         const int fit = (int)(((int64_t)1 << 26) / (g.nfft * (int64_t)s->elem));
-        if (max_batch <= 0 && max_batch != POND_BATCH_AUTOTUNE && fit > g.max_batch && e == hipSuccess) {
-            const size_t bytes = (size_t)fit * g.nfft * s->elem;
-            if (hipMalloc(&g.spec, bytes) == hipSuccess && hipMalloc(&g.out, bytes) == hipSuccess) {
-                g.max_batch = fit;
-            } else {  // no room for more than the usual count
-                (void)hipGetLastError();
-                if (g.spec) (void)hipFree(g.spec);
-                g.spec = g.out = nullptr;
-            }
-        }
-        if (!g.spec) {
-            chk(hipMalloc(&g.spec, (size_t)g.max_batch * g.nfft * s->elem));
-            chk(hipMalloc(&g.out, (size_t)g.max_batch * g.nfft * s->elem));
-        }
+        g.most_batch = max_batch <= 0 && max_batch != POND_BATCH_AUTOTUNE && fit > g.max_batch ? fit : g.max_batch;
+        if (e == hipSuccess) chk(g.area.create(g.max_batch, g.most_batch, 2 * (size_t)g.nfft * s->elem));
         // Packed float16: power scale 256 over the measured gain of the
         // group's float16 path (forward rows, then the inverse rows of the
         // group's first trial; every trial's chirp rounds alike).
@@ -380,27 +371,27 @@ pond_search* pond_search_create_ex(double f0_mhz, double bw_mhz, const double* d
             cal.log2n1 = g.log2n1;
             cal.log2n2 = g.log2n2;
             cal.tw2 = g.tw2;
-            cal.work = g.spec;
-            cal.max_batch = g.max_batch;
+            cal.work = g.spec();
+            cal.max_batch = (int)g.area.blocks;
             cal.f16_cols = 2 * g.hop == g.nfft;
             double gain = 1.0;
             chk(half_power_gain(
                 cal,
                 [&](int nb, const void** res) {
                     K2Args f{};
-                    f.work = g.spec;
+                    f.work = g.spec();
                     f.nblocks = nb;
                     f.log2n2 = g.log2n2;
                     f.tw1 = g.tw1;
                     f.htw4 = g.htw4;
                     hipError_t r = launch_k2(precision, kRowFwd, g.log2n1, f, nullptr);
                     K2Args v = f;
-                    v.in = g.spec;
-                    v.out = g.out;
+                    v.in = g.spec();
+                    v.out = g.out(s->elem);
                     v.geo = g.geo;
                     v.dm = s->dm[g.trials[0]];
                     if (r == hipSuccess) r = launch_k2(precision, kRowInv, g.log2n1, v, nullptr);
-                    *res = g.out;
+                    *res = g.out(s->elem);
                     return r;
                 },
                 &gain));
@@ -470,9 +461,10 @@ int32_t pond_search_run(pond_search* s, const int8_t* iq, int64_t nsamp, float* 
     ReduceQueue rq;
     for (auto& g : s->groups) {
         const int64_t nb_total = nsamp < g.nfft ? 0 : (nsamp - g.nfft) / g.hop + 1;
-        for (int64_t b = 0; b < nb_total; b += g.max_batch) {
-            const int nb = (int)(nb_total - b < g.max_batch ? nb_total - b : g.max_batch);
-            e = run_group(s, g, g.spec, g.out, iq, b, nb, g.trials.size(), stream, rq);
+        if (g.most_batch > g.area.blocks) g.area.grow(nb_total, g.most_batch, stream);
+        for (int64_t b = 0; b < nb_total; b += g.area.blocks) {
+            const int nb = (int)(nb_total - b < g.area.blocks ? nb_total - b : g.area.blocks);
+            e = run_group(s, g, g.spec(), g.out(s->elem), iq, b, nb, g.trials.size(), stream, rq);
             if (e != hipSuccess) return fail();
         }
     }
