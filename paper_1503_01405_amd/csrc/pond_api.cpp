@@ -85,10 +85,12 @@ struct pond_plan {
     // elements, the filter and fold in real samples.
     int32_t kind = POND_INPUT_COMPLEX;
     int bpe = 2;                // input bytes per element
-    // Tables of its middle pass (RealPairArgs), n2/2 + 1 rows of n1 each; or,
-    // float16 storage with rows of 2^14, three passes (real_three): tw4 for
-    // all rows and rtab = (split twiddle, filter).
+    // Tables of its middle pass, one allocation (real_tab; each of its own would be
+    // as slow to allocate and release as all of them): RealPairArgs, n2/2 + 1 rows of
+    // n1 each; or, float16 storage with rows of 2^14, three passes (real_three): tw4
+    // for all rows and rtab = (split twiddle, filter).
     bool real_three = false;
+    void* real_tab = nullptr;
     float2* tw4 = nullptr;
     float4* real_ad = nullptr;
     float2* real_b = nullptr;
@@ -204,9 +206,8 @@ void free_plan_memory(pond_plan* p) {
     for (hipEvent_t e : p->event_pool) (void)hipEventDestroy(e);
     p->event_pool.clear();
     p->work.release();
-    void* ptrs[] = {p->tail[0], p->tail[1], p->tw1,    p->tw2,     p->table,   p->htable,  p->tw4,      p->real_ad,
-                    p->real_b,  p->rtab,    p->tw_ck,  p->tw_hi,   p->tw_lo,   p->acc_sum, p->acc_cnt,  p->part_sum,
-                    p->part_cnt, p->status, p->chirp_split};
+    void* ptrs[] = {p->tail[0], p->tail[1], p->tw1,     p->tw2,     p->table,    p->htable,   p->real_tab, p->tw_ck,
+                    p->tw_hi,   p->tw_lo,   p->acc_sum, p->acc_cnt, p->part_sum, p->part_cnt, p->status, p->chirp_split};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
 }
@@ -734,14 +735,19 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     if (kind != POND_INPUT_COMPLEX) {
         p->real_three = precision == POND_MIXED_VALU && p->log2n1 == kMaxLog2RowN1;
         const size_t entries = (size_t)(p->real_three ? n2 : n2 / 2 + 1) * (size_t)n1;
-        chk(hipMalloc(reinterpret_cast<void**>(&p->tw4), entries * sizeof(float2)));
-        if (p->real_three) {
-            chk(hipMalloc(reinterpret_cast<void**>(&p->rtab), (size_t)(nfft + 1) * sizeof(float4)));
-            if (e == hipSuccess)
+        const size_t wide = p->real_three ? (size_t)(nfft + 1) : entries;  // of rtab or real_ad
+        const size_t bytes = wide * sizeof(float4) + (p->real_three ? 1 : 2) * entries * sizeof(float2);
+        chk(hipMalloc(&p->real_tab, bytes));
+        if (e == hipSuccess) {
+            float4* const first = static_cast<float4*>(p->real_tab);
+            p->tw4 = reinterpret_cast<float2*>(first + wide);
+            if (p->real_three) {
+                p->rtab = first;
                 chk(launch_k2_build_split_tables(p->tw4, nullptr, p->log2n1, p->log2n2, 0.0, p->f0, p->df, nullptr));
-        } else {
-            chk(hipMalloc(reinterpret_cast<void**>(&p->real_ad), entries * sizeof(float4)));
-            chk(hipMalloc(reinterpret_cast<void**>(&p->real_b), entries * sizeof(float2)));
+            } else {
+                p->real_ad = first;
+                p->real_b = p->tw4 + entries;
+            }
         }
     } else if (p->log2m2) {
         // chirp_split, above
