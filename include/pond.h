@@ -97,7 +97,9 @@ typedef struct pond_info {
     int64_t n1, n2;        /* four-step factorisation nfft = n1 * n2 (row x col)   */
     int64_t samples_in;    /* input samples appended since the stream started     */
     int64_t outputs_done;  /* outputs produced since the stream started           */
-    int64_t max_batch;     /* blocks per launch, as given, tuned or by default      */
+    int64_t max_batch;     /* blocks per launch, as given or tuned; else the usual   */
+                           /* count (calls then launch more short blocks at once    */
+                           /* and fewer long ones)                                  */
     double  fs_hz;         /* complex sample rate                                  */
     double  delta_lo_s;    /* delay of band bottom relative to f0                  */
     double  delta_hi_s;    /* advance of band top relative to f0                   */
@@ -192,9 +194,9 @@ pond_plan* pond_plan_create(double f0_mhz, double bw_mhz, double dm,
  * pseudo-random int8 input streamed from a ring of 1 GiB (temporarily
  * allocated, less if the device lacks six times that free; each timed
  * run reads samples that no earlier run left in the caches) at 1, 2, 3,
- * 4, 6, 8, 12, 16, 24 and 32 blocks per launch (those
- * whose work area fits in min(4 GiB, a third of the free device memory),
- * plus the default) during creation and
+ * 4, 6, 8, 12, 16, 24, 32 and, short blocks, 64 and on to what an untuned
+ * plan launches at once (those whose work area fits in min(4 GiB, a third
+ * of the free device memory), plus the default) during creation and
  * keep the fastest per block, a larger launch winning only by more than 0.5%;
  * other values <= 0 pick the default (2^29 bytes of work area, 1 .. 16
  * blocks; calls with more of the shorter blocks enlarge the work area, up to 2^27
@@ -212,8 +214,9 @@ pond_plan* pond_plan_create_ex(double f0_mhz, double bw_mhz, double dm,
 /*
  * The autotuner's result for a plan created with POND_BATCH_AUTOTUNE: the
  * blocks per launch it chose and their measured time per block (ms), the
- * default rule's batch and its measured time per block, and whether the
- * choice came from the cache (1; its times are those of the measuring run).
+ * usual count (pond_info.max_batch of a plan left to the library) and its
+ * measured time per block, and whether the choice came from the cache (1;
+ * its times are those of the measuring run).
  * POND_EINVAL for a null plan or one created without the tuner.
  */
 int32_t pond_plan_autotune(const pond_plan* p, int32_t* batch, double* ms_per_block,

@@ -315,6 +315,7 @@ hipError_t run_blocks(pond_plan* p, void* work, const int8_t* in, int nb, float*
 }
 
 int default_max_batch(int64_t nfft, int32_t precision, int32_t max_batch);
+int cached_batch(int64_t nfft, int32_t precision, int32_t kind, int max_batch);
 
 // Autotuned blocks per launch of a complex-input plan (tables, twiddles and
 // fold buffers in place, p->work not yet allocated): candidates whose work
@@ -328,7 +329,8 @@ hipError_t tune_plan(pond_plan* p) {
     const int64_t block_bytes = p->nfft * (int64_t)p->elem;
     const int64_t cap = std::min<int64_t>((int64_t)4 << 30, (int64_t)(free_b / 3));
     const int dflt = default_max_batch(p->nfft, p->precision, 0);
-    const std::vector<int> cand = batch_candidates(block_bytes, cap, dflt);
+    const std::vector<int> cand =
+        batch_candidates(block_bytes, cap, dflt, cached_batch(p->nfft, p->precision, p->kind, dflt));
     const int nb_max = cand.back();
     void* work = nullptr;
     int8_t* in = nullptr;

@@ -204,6 +204,18 @@ hipError_t run_group(const pond_search* s, const Group& g, void* spec, void* out
     return hipSuccess;
 }
 
+// Blocks that a run of an untuned group launches at most.  Short blocks go as many
+// to a launch as half the Infinity Cache holds of spectrum and output.  0.25 s, 8
+// trials, launches of 16 blocks, of half the rule's count and of that, us: packed
+// float16 2^12 11,229, 408 and 407 (4,096), 2^14 2,999, 364 and 358, 2^16 950, 324
+// and 325, 2^18 437, 336 and 338; float32 2^12 538 and 445 (2,048), 2^14 3,068, 456
+// and 390, 2^16 1,085, 432 and 372.
+int untuned_batch(const pond_search& s, const Group& g) {
+    const int64_t b = ((int64_t)1 << 28) / (g.nfft * (int64_t)s.elem);
+    const int64_t fit = ((int64_t)1 << 26) / (g.nfft * (int64_t)s.elem);
+    return (int)std::max(std::max<int64_t>(1, std::min<int64_t>(b, 16)), fit);
+}
+
 // Autotuned blocks per launch of one group (tables built, fold buffers in
 // place, spec/out not allocated): the group's pass with two trials (the
 // per-trial part is the same for every trial) on pseudo-random input.
@@ -213,7 +225,7 @@ hipError_t tune_group(pond_search* s, Group& g, int default_batch) {
     if (e != hipSuccess) return e;
     const int64_t block_bytes = 2 * g.nfft * (int64_t)s->elem;  // spec + out
     const int64_t cap = std::min<int64_t>((int64_t)4 << 30, (int64_t)(free_b / 3));
-    const std::vector<int> cand = batch_candidates(block_bytes, cap, default_batch);
+    const std::vector<int> cand = batch_candidates(block_bytes, cap, default_batch, untuned_batch(*s, g));
     const int nb_max = cand.back();
     void *spec = nullptr, *out = nullptr;
     int8_t* in = nullptr;
@@ -354,13 +366,7 @@ pond_search* pond_search_create_ex(double f0_mhz, double bw_mhz, const double* d
         }
         if (e == hipSuccess) chk(launch_build_dm_geometry(g.geo, g.log2n1, g.log2n2, f0_mhz, df, nullptr));
         if (e == hipSuccess && max_batch == POND_BATCH_AUTOTUNE) chk(tune_group(s, g, g.max_batch));
-        // Left to the library, short blocks go as many to a launch as half the
-        // Infinity Cache holds of spectrum and output.  0.25 s, 8 trials, launches
-        // of 16 blocks and of the rule's count, us: packed float16 2^12 11,229 and
-        // 499 (1,024; the rule 4,096), 2^14 2,977 and 373, 2^16 948 and 337, 2^18
-        // 443 and 354; float32 2^16 1,078 and 382.
-        const int fit = (int)(((int64_t)1 << 26) / (g.nfft * (int64_t)s->elem));
-        g.most_batch = max_batch <= 0 && max_batch != POND_BATCH_AUTOTUNE && fit > g.max_batch ? fit : g.max_batch;
+        g.most_batch = max_batch > 0 || max_batch == POND_BATCH_AUTOTUNE ? g.max_batch : untuned_batch(*s, g);
         if (e == hipSuccess) chk(g.area.create(g.max_batch, g.most_batch, 2 * (size_t)g.nfft * s->elem));
         // Packed float16: power scale 256 over the measured gain of the
         // group's float16 path (forward rows, then the inverse rows of the

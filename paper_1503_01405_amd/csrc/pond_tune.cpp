@@ -35,7 +35,7 @@ std::string device_tag(int dev) {
 
 std::string key_line(const TuneKey& k, const std::string& dev) {
     char buf[256];
-    std::snprintf(buf, sizeof buf, "pond-tune-4 %s %s nfft=%lld form=%d kind=%d hist=%s", dev.c_str(), k.path,
+    std::snprintf(buf, sizeof buf, "pond-tune-5 %s %s nfft=%lld form=%d kind=%d hist=%s", dev.c_str(), k.path,
                   (long long)k.nfft, k.precision, k.kind, k.global_hist ? "global" : "lds");
     return buf;
 }
@@ -150,11 +150,18 @@ TuneRing tune_ring(int64_t nfft, int64_t hop, int64_t bytes_per_sample, int nb_m
     return r;
 }
 
-std::vector<int> batch_candidates(int64_t block_bytes, int64_t cap_bytes, int default_batch) {
+std::vector<int> batch_candidates(int64_t block_bytes, int64_t cap_bytes, int default_batch, int untuned) {
     std::vector<int> c;
+    auto add = [&](int nb) {
+        if (std::find(c.begin(), c.end(), nb) == c.end()) c.push_back(nb);
+    };
+    auto fits = [&](int nb) { return (int64_t)nb * block_bytes <= cap_bytes || nb == 1; };
     for (int nb : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32})
-        if ((int64_t)nb * block_bytes <= cap_bytes || nb == 1) c.push_back(nb);
-    if (std::find(c.begin(), c.end(), default_batch) == c.end()) c.push_back(default_batch);
+        if (fits(nb)) add(nb);
+    for (int nb = 64; nb <= untuned; nb *= 2)
+        if (fits(nb)) add(nb);
+    if (fits(untuned)) add(untuned);
+    add(default_batch);
     std::sort(c.begin(), c.end());
     return c;
 }

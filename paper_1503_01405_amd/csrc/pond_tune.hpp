@@ -21,7 +21,7 @@ struct TuneKey {
 struct TuneResult {
     int batch = 0;                      // chosen blocks per launch
     double ms_per_block = 0;            // its time per block
-    int default_batch = 0;              // the fixed rule's choice
+    int default_batch = 0;              // the usual count (untuned calls launch more short blocks, fewer long ones)
     double default_ms_per_block = 0;    // its time per block
     bool from_cache = false;            // read from POND_AUTOTUNE_CACHE, not measured
 };
@@ -47,8 +47,9 @@ struct TuneRing {
 };
 TuneRing tune_ring(int64_t nfft, int64_t hop, int64_t bytes_per_sample, int nb_max, int64_t spare_bytes);
 
-// 1, 2, 3, 4, 6, 8, 12, 16, 24, 32 blocks where they fit in cap_bytes (1
-// always), plus the default.
-std::vector<int> batch_candidates(int64_t block_bytes, int64_t cap_bytes, int default_batch);
+// 1, 2, 3, 4, 6, 8, 12, 16, 24, 32 blocks, the powers of two from 64 to what an
+// untuned call launches at most, and that, where they fit in cap_bytes (1 always),
+// plus the default.
+std::vector<int> batch_candidates(int64_t block_bytes, int64_t cap_bytes, int default_batch, int untuned);
 
 }  // namespace pond
