@@ -422,8 +422,6 @@ int64_t launch_blocks(int64_t left, int64_t batch, int64_t room) {
     return (left + launches - 1) / launches;
 }
 
-constexpr int64_t kFullBins = 1024;  // bins of sub-integrations one large launch folds into
-
 int64_t n_blocks_for(int64_t nsamp, int64_t nfft, int64_t hop) {
     return nsamp < nfft ? 0 : (nsamp - nfft) / hop + 1;
 }
@@ -1124,45 +1122,30 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     // call has up to launch_batch.
     if (p->launch_batch > p->work.blocks) p->work.grow(nb_total - b, p->launch_batch, stream);
     const int64_t batch = std::min<int64_t>(p->launch_batch, p->work.blocks);
-    // Blocks of the launch that begins with block `at`.  Sub-integrations bound it:
-    // as many blocks as touch no more of them than the histogram in LDS holds (one
-    // block, or a single sub-integration beyond it: any number, in global memory).
-    // `many` (more than max_batch blocks): no more entries of several
-    // sub-integrations than leave K3 its workgroups per CU, unless max_batch blocks
-    // with all of the LDS are more.
-    auto blocks_at = [&](int64_t at, bool many) -> int64_t {
-        const int64_t left = nb_total - at;
-        const int64_t want = p->given ? std::min<int64_t>(left, p->max_batch)
-                             : many   ? launch_blocks(left, batch, batch)
-                                      : launch_blocks(left, std::min<int64_t>(batch, p->max_batch), p->max_batch);
-        if (subint <= 0 || nbins > p->hist_cap) return want;
-        const int64_t s0 = at * hop / subint;
-        auto within = [&](int64_t blocks, int64_t cap) {
-            const int64_t room = cap / nbins;
-            if (((at + blocks) * hop - 1) / subint - s0 < room) return blocks;
-            return std::max<int64_t>(1, (s0 + room) * subint / hop - at);
-        };
-        int64_t fit = within(std::min<int64_t>(want, p->max_batch), p->hist_cap);
-        if (many) fit = std::max(fit, within(want, std::min(p->hist_cap, std::max<int64_t>(nbins, kFullBins))));
-        return fit < want ? launch_blocks(left, fit, fit) : want;
-    };
-    // Larger launches only where they are fewer (47 blocks of 2^20, sub-integrations
-    // of 1.5 blocks: 24, 12 and 11 blocks 379 us, 16, 16 and 15 of them 357).
-    bool many = batch > p->max_batch;
-    if (many && subint > 0 && nbins <= p->hist_cap) {
-        auto launches = [&](bool m) {
-            int64_t k = 0;
-            for (int64_t at = b; at < nb_total; at += blocks_at(at, m)) ++k;
-            return k;
-        };
-        many = launches(true) < launches(false);
-    }
     ReduceQueue rq;
     int64_t rq_blocks = 0;  // blocks whose fold partials are queued
     while (b < nb_total) {
-        const int64_t nb = blocks_at(b, many);
-        const int64_t s_lo = subint > 0 ? b * hop / subint : 0;
-        const int64_t nsub = subint > 0 ? ((b + nb) * hop - 1) / subint - s_lo + 1 : 1;
+        const int64_t left = nb_total - b;
+        int64_t nb = p->given ? std::min<int64_t>(left, p->max_batch)
+                              : launch_blocks(left, batch, std::max<int64_t>(batch, p->max_batch));
+        int64_t s_lo = 0, nsub = 1;
+        if (subint > 0) {
+            s_lo = b * hop / subint;
+            auto touched = [&] { return ((b + nb) * hop - 1) / subint - s_lo + 1; };
+            // As many blocks as touch no more sub-integrations than the histogram in
+            // LDS holds, what is left shared evenly (one block, or a single
+            // sub-integration beyond it: in global memory, any number).  A full
+            // histogram costs K3 its second workgroup per CU and is still worth the
+            // blocks (10,000 of 2^12, 512 bins, 30 blocks a sub-integration, float32:
+            // 1,699 us a call, 8,817 in launches of up to 1,024 entries).
+            const int64_t room = p->hist_cap / nbins;
+            if (room > 0 && touched() > room) {
+                const int64_t fit = std::max<int64_t>(1, (s_lo + room) * subint / hop - b);
+                const int64_t launches = (left + fit - 1) / fit;
+                nb = (left + launches - 1) / launches;
+            }
+            nsub = touched();
+        }
         const int64_t entries = nsub * nbins;
         const bool global_mode = entries > p->hist_cap;
 
