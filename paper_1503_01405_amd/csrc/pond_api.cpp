@@ -411,6 +411,12 @@ int cached_batch(int64_t nfft, int32_t precision, int32_t kind, int max_batch) {
     return (int)std::min<int64_t>(max_batch, std::max<int64_t>(3, fit));
 }
 
+// Blocks of the work area of such a plan: what its launches take (launch_blocks: less
+// than two cached counts at once).
+int held_blocks(int64_t nfft, int32_t precision, int32_t kind, int max_batch) {
+    return std::min(max_batch, 2 * cached_batch(nfft, precision, kind, max_batch) - 1);
+}
+
 // Blocks of the next launch of `left` where the library chooses (a stated or tuned
 // count is launched as it is): no short launch at the end.  Less than two launches'
 // worth goes at once where the work area (room blocks) holds it, else in equal parts
@@ -563,7 +569,7 @@ int64_t plan_footprint(int64_t nfft, int32_t nbins, int32_t precision, int32_t m
     const int log2n2 = log2n / 2 < kMaxLog2N2 ? log2n / 2 : kMaxLog2N2;
     const int64_t n1 = (int64_t)1 << (log2n - log2n2), n2 = (int64_t)1 << log2n2;
     const int64_t elem = precision == POND_FP32 ? 8 : 4;
-    const int64_t mb = default_max_batch(nfft, precision, max_batch);
+    const int64_t mb = held_blocks(nfft, precision, POND_INPUT_COMPLEX, default_max_batch(nfft, precision, max_batch));
     const bool split = (log2n - log2n2) > kMaxLog2RowN1;
     // float2 chirp (float32), two float16 pairs (float16 arithmetic), float4 otherwise
     int64_t tables = nfft * (precision == POND_FP32 || f16_arith(precision) ? 8 : 16) + (n1 + n2) * 8;
@@ -768,7 +774,8 @@ pond_plan* create_plan(double f0_mhz, double bw_mhz, double dm, int64_t nfft, in
     p->launch_batch = p->given ? p->max_batch : cached_batch(nfft, precision, kind, p->max_batch);
     // (a server's plan is charged for max_batch blocks)
     if (acc_slots > 0) p->launch_batch = std::min(p->launch_batch, p->max_batch);
-    if (e == hipSuccess) chk(p->work.create(p->max_batch, p->launch_batch, (size_t)nfft * p->elem));
+    const int held = p->given ? p->max_batch : held_blocks(nfft, precision, kind, p->max_batch);
+    if (e == hipSuccess) chk(p->work.create(held, p->launch_batch, (size_t)nfft * p->elem));
     // Float16 arithmetic (packed float16 and matrix-core forms): the power
     // scale is 256 over the measured gain of the plan's float16 arithmetic
     // (the unit-taper table just built).
@@ -1127,7 +1134,7 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     while (b < nb_total) {
         const int64_t left = nb_total - b;
         int64_t nb = p->given ? std::min<int64_t>(left, p->max_batch)
-                              : launch_blocks(left, batch, std::max<int64_t>(batch, p->max_batch));
+                              : launch_blocks(left, batch, p->work.blocks);
         int64_t s_lo = 0, nsub = 1;
         if (subint > 0) {
             s_lo = b * hop / subint;
