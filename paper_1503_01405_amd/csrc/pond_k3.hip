@@ -342,12 +342,13 @@ k3_colinv_detect_fold(K3Args args) {
             const double y0 = (x0 - fl) * a.nbins_d;
             const int bin0 = min((int)y0, a.nbins - 1);
             const double next = (double)(bin0 + 1);
-            // Sub-integration of the group, if the launch spans more than one;
-            // its 16 outputs share it unless it ends within them.
+            // Sub-integration of the group, if the launch spans more than one (in
+            // global memory the entries may be more than an int32 counts); its 16
+            // outputs share it unless it ends within them.
             int sub0 = 0;
             bool one_sub = true;
             const int64_t d0 = m0 - a.s_base * a.subint;
-            if (a.subint > 0 && a.entries != a.nbins) {
+            if (a.subint > 0 && (a.global_mode || a.entries != a.nbins)) {
                 sub0 = (int)subint_rel(d0, a.subint, a.inv_subint);
                 one_sub = d0 - sub0 * a.subint + 15 < a.subint;
             }
