@@ -396,10 +396,11 @@ int default_max_batch(int64_t nfft, int32_t precision, int32_t max_batch) {
 // blocks 4.12, 16 4.84).
 // Short blocks go more than max_batch to a launch, as many as that half holds:
 // 16 blocks of 2^12 are 64 column tiles for 256 CUs.  2 s (32 M samples), in
-// launches of 16 blocks and of the rule's count, us: float32 2^12 17,186 and 695
-// (1,024; the rule 4,096), 2^14 4,913 and 435, 2^16 1,679 and 423, 2^18 463 and
-// 328 (twice the rule 346); packed float16 2^16 1,329 and 300, 2^18 368 and 219;
-// real input of 2^15 points 2,464 and 309, 2^19 234 and 173.
+// launches of 16 blocks, of half the rule's count and of that, us: float32 2^12
+// 17,186, 564 and 477 (4,096), 2^14 4,910, 477 and 417, 2^16 1,678, 472 and 410,
+// 2^18 462, 376 and 316 (twice the rule 346); packed float16 2^14 4,626, 411 and
+// 368, 2^16 1,336, 308 and 266, 2^18 376, 234 and 208; real input of 2^15 points
+// 2,652, 361 and 281, 2^19 415 and 294.
 int cached_batch(int64_t nfft, int32_t precision, int32_t kind, int max_batch) {
     const int64_t elem = precision == POND_FP32 ? 8 : 4;
     const int log2n = ilog2(nfft);

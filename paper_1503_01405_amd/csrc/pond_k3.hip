@@ -93,7 +93,7 @@ k3_colinv_detect_fold(K3Args args) {
     uint32_t* hcnt = reinterpret_cast<uint32_t*>(dyn_u64 + (args.global_mode ? 0 : args.entries));
     constexpr bool H16 = FORM == kFormF16 || FORM == kFormMfma;  // float16 arithmetic
     constexpr bool MX = FORM == kFormMfma && kMxShape<LOG2N2, true>;  // radix-16 sums on matrix cores
-    static_assert(!WIDE || (H16 && !REAL), "32-column tiles: float16 arithmetic");
+    static_assert(!WIDE || (MX && !REAL), "32-column tiles: matrix-core form");
     constexpr int W = WIDE ? 2 : 1;  // adjacent columns per thread, groups of 16 outputs per row
     using V = std::conditional_t<WIDE, hh2, std::conditional_t<H16, h2, float2>>;
     V* const tile = reinterpret_cast<V*>(lds_raw);
