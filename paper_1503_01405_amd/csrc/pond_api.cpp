@@ -1130,30 +1130,38 @@ static int64_t run_call(pond_plan* p, const int8_t* iq, int64_t nsamp, int64_t s
     // call has up to launch_batch.
     if (p->launch_batch > p->work.blocks) p->work.grow(nb_total - b, p->launch_batch, stream);
     const int64_t batch = std::min<int64_t>(p->launch_batch, p->work.blocks);
+    // Blocks of the launch that begins with block `at`: as many as touch no more
+    // sub-integrations than the histogram in LDS holds (one block, or a single
+    // sub-integration beyond it: in global memory, any number).  A full histogram
+    // costs K3 its second workgroup per CU and is still worth the blocks (10,000 of
+    // 2^12, 512 bins, 30 blocks a sub-integration, float32: 1,699 us a call, 8,817 in
+    // launches of up to 1,024 entries).
+    const int64_t room = p->hist_cap / nbins;
+    auto blocks_at = [&](int64_t at, bool even) -> int64_t {
+        const int64_t left = nb_total - at;
+        const int64_t want = p->given ? std::min<int64_t>(left, p->max_batch) : launch_blocks(left, batch, p->work.blocks);
+        if (subint <= 0 || room == 0) return want;
+        const int64_t s0 = at * hop / subint;
+        if (((at + want) * hop - 1) / subint - s0 < room) return want;
+        const int64_t fit = std::max<int64_t>(1, (s0 + room) * subint / hop - at);
+        const int64_t launches = (left + fit - 1) / fit;
+        return even ? (left + launches - 1) / launches : fit;
+    };
+    // Bounded launches share the blocks evenly (47 blocks of 2^20, half a block a
+    // sub-integration: 16, 16 and 15 blocks 404 us, 21, 21 and 5 of them 434), unless
+    // they then fall across more sub-integrations and are more.
+    auto launches = [&](bool even) {
+        int64_t k = 0;
+        for (int64_t at = b; at < nb_total; at += blocks_at(at, even)) ++k;
+        return k;
+    };
+    const bool even = subint <= 0 || launches(true) <= launches(false);
     ReduceQueue rq;
     int64_t rq_blocks = 0;  // blocks whose fold partials are queued
     while (b < nb_total) {
-        const int64_t left = nb_total - b;
-        int64_t nb = p->given ? std::min<int64_t>(left, p->max_batch)
-                              : launch_blocks(left, batch, p->work.blocks);
-        int64_t s_lo = 0, nsub = 1;
-        if (subint > 0) {
-            s_lo = b * hop / subint;
-            auto touched = [&] { return ((b + nb) * hop - 1) / subint - s_lo + 1; };
-            // As many blocks as touch no more sub-integrations than the histogram in
-            // LDS holds, what is left shared evenly (one block, or a single
-            // sub-integration beyond it: in global memory, any number).  A full
-            // histogram costs K3 its second workgroup per CU and is still worth the
-            // blocks (10,000 of 2^12, 512 bins, 30 blocks a sub-integration, float32:
-            // 1,699 us a call, 8,817 in launches of up to 1,024 entries).
-            const int64_t room = p->hist_cap / nbins;
-            if (room > 0 && touched() > room) {
-                const int64_t fit = std::max<int64_t>(1, (s_lo + room) * subint / hop - b);
-                const int64_t launches = (left + fit - 1) / fit;
-                nb = (left + launches - 1) / launches;
-            }
-            nsub = touched();
-        }
+        const int64_t nb = blocks_at(b, even);
+        const int64_t s_lo = subint > 0 ? b * hop / subint : 0;
+        const int64_t nsub = subint > 0 ? ((b + nb) * hop - 1) / subint - s_lo + 1 : 1;
         const int64_t entries = nsub * nbins;
         const bool global_mode = entries > p->hist_cap;
 
