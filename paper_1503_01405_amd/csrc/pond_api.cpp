@@ -456,7 +456,7 @@ hipError_t WorkArea::create(int64_t usual, int64_t most, size_t bytes) {
 }
 
 void WorkArea::grow(int64_t want, int64_t most, hipStream_t stream) {
-    if (full || want <= blocks || blocks >= most) return;
+    if (full || nold == kMaxOld || want <= blocks || blocks >= most) return;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
@@ -476,14 +476,13 @@ void WorkArea::grow(int64_t want, int64_t most, hipStream_t stream) {
         full = true;
         return;
     }
-    old.push_back(ptr);
+    old[nold++] = ptr;
     ptr = q;
     blocks = n;
 }
 
 void WorkArea::release() {
-    for (void* q : old) (void)hipFree(q);
-    old.clear();
+    while (nold > 0) (void)hipFree(old[--nold]);
     if (ptr) (void)hipFree(ptr);
     ptr = nullptr;
     blocks = 0;

@@ -7,7 +7,6 @@
 #include <stdint.h>
 
 #include <functional>
-#include <vector>
 
 struct pond_plan;
 
@@ -313,7 +312,9 @@ struct WorkArea {
     int64_t blocks = 0;
     size_t block_bytes = 0;
     bool full = false;          // the device had no room for more
-    std::vector<void*> old;
+    static constexpr int kMaxOld = 8;  // (doublings from kSmallArea to 2^27 bytes are 3)
+    void* old[kMaxOld] = {};
+    int nold = 0;
     static constexpr size_t kLargeArea = (size_t)1 << 25, kSmallArea = (size_t)1 << 24;
     hipError_t create(int64_t usual, int64_t most, size_t bytes);
     // Room for min(want, most) blocks, if it can be had: not while the stream is
