@@ -81,7 +81,7 @@ __device__ __forceinline__ void k3_fold_add(K3Kernarg& a, uint64_t* hsum, uint32
 // 13.9 in launches of 4 / 8; packed float16 gains nothing from it.  A reduction of
 // the powers across lanes in place of the LDS buffer (four DPP steps) cost 25%
 // more VALU instructions and 8% more time.
-template <int LOG2N2, class T, int FORM, bool REAL, bool TWO, bool WIDE>
+template <int LOG2N2, class T, int FORM, bool REAL, bool TWO, bool WIDE, bool AHEAD>
 __global__ void __launch_bounds__(1 << LOG2N2) __attribute__((amdgpu_waves_per_eu(TWO ? 8 : 4)))
 k3_colinv_detect_fold(K3Args args) {
     using Sh = K3Shape<LOG2N2>;
@@ -132,15 +132,15 @@ k3_colinv_detect_fold(K3Args args) {
 
     // The column tile of an item, as stored.  Where one workgroup has the CU
     // (TWO: two share it and hide each other's loads), the next item's tile
-    // is loaded while this one is transformed and folded, if it is 64 bytes a
-    // thread: the 128 of float32 and of WIDE cost more than they hide where the
+    // is loaded while this one is transformed and folded (AHEAD), if it is 64 bytes
+    // a thread: the 128 of float32 and of WIDE cost more than they hide where the
     // launch's work area is cached (2^23, per block in launches of 1 / 3 / 8:
     // float32 28.9 / 19.5 / 21.8 us with the read-ahead, 24.7 / 18.4 / 22.5
     // without; matrix-core form of 1 / 4 / 8: 19.7 / 15.0 / 14.6 and 19.1 / 13.7 /
-    // 13.9).  WIDE: a thread's two
+    // 13.9).  Float32 reads ahead where it is not (kAheadBytes).  WIDE: a thread's two
     // columns are one 8-byte access (4-byte aligned), but for the pair that
     // crosses n1 (r0 odd), whose second column is column 0.
-    constexpr bool kPrefetch = !TWO && !WIDE && LOG2N2 >= 9 && sizeof(T) == 4;
+    constexpr bool kPrefetch = AHEAD && !TWO && !WIDE && LOG2N2 >= 9;
     using Raw = std::conditional_t<WIDE, hh2, std::conditional_t<H16, h2, T>>;
     auto load_tile = [&](int it, Raw(&dst)[16]) {
         const int bb = it >> log2tiles;
@@ -424,10 +424,10 @@ k3_colinv_detect_fold(K3Args args) {
     }
 }
 
-template <class T, int FORM, int LOG2N2, bool REAL, bool TWO, bool WIDE = false>
+template <class T, int FORM, int LOG2N2, bool REAL, bool TWO, bool WIDE = false, bool AHEAD = sizeof(T) == 4>
 static hipError_t k3_launch(const K3Args& a, int grid, size_t dyn, hipStream_t s) {
     static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k3_colinv_detect_fold<LOG2N2, T, FORM, REAL, TWO, WIDE>),
+        reinterpret_cast<const void*>(&k3_colinv_detect_fold<LOG2N2, T, FORM, REAL, TWO, WIDE, AHEAD>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)(160 * 1024 - K3Shape<LOG2N2>::lds(FORM, WIDE)));
     if (attr != hipSuccess) return attr;
     K3Args c = a;
@@ -437,7 +437,7 @@ static hipError_t k3_launch(const K3Args& a, int grid, size_t dyn, hipStream_t s
     c.fold_safe1 = 1e-15 * (double)a.nbins;
     c.samples_per_bin = 1.0 / per_sample;
     c.inv_subint = a.subint > 0 ? 1.0 / (double)a.subint : 0.0;
-    hipLaunchKernelGGL((k3_colinv_detect_fold<LOG2N2, T, FORM, REAL, TWO, WIDE>), dim3(grid), dim3(1 << LOG2N2), dyn,
+    hipLaunchKernelGGL((k3_colinv_detect_fold<LOG2N2, T, FORM, REAL, TWO, WIDE, AHEAD>), dim3(grid), dim3(1 << LOG2N2), dyn,
                        s, c);
     return hipGetLastError();
 }
@@ -448,6 +448,8 @@ constexpr int64_t kWideItems = 256;
 static bool k3_wide(bool mfma, int log2n2, int64_t items, size_t dyn) {
     return mfma && log2n2 == 10 && items / 2 >= kWideItems && K3Shape<10>::LDS_WIDE + dyn <= kLdsBytes;
 }
+
+constexpr int64_t kAheadBytes = 1ll << 28;  // of work area in a launch: the Infinity Cache
 
 template <class T, int FORM, int LOG2N2>
 static hipError_t k3_one(const K3Args& a, int grid, size_t dyn, hipStream_t s) {
@@ -462,6 +464,14 @@ static hipError_t k3_one(const K3Args& a, int grid, size_t dyn, hipStream_t s) {
     if constexpr (FORM == kFormF16 && LOG2N2 >= 9) {
         if (2 * (K3Shape<LOG2N2>::lds(FORM) + dyn) <= kLdsBytes)
             return k3_launch<T, FORM, LOG2N2, false, true>(a, grid, dyn, s);
+    }
+    // Float32: beyond the 256 MB Infinity Cache the work area comes from memory, and
+    // the read-ahead pays (512 MB: 2^23 21.8 us a block against 22.5, 2^24 48.3 and
+    // 48.8; 256 MB 21.9 and 21.8, 48.6 and 48.8; 2^26, DM 130, the call 4,793 and
+    // 4,817 us).
+    if constexpr (FORM == kFormF32 && LOG2N2 == 10 && sizeof(T) == 8) {
+        if (((int64_t)a.nblocks << (a.log2n1 + LOG2N2)) * (int64_t)sizeof(T) > kAheadBytes)
+            return k3_launch<T, FORM, LOG2N2, false, false, false, true>(a, grid, dyn, s);
     }
     return k3_launch<T, FORM, LOG2N2, false, false>(a, grid, dyn, s);
 }

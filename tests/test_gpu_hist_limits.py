@@ -46,3 +46,13 @@ def test_histogram_limits(form, log2n, nbins):
     print(f"{form}: profile rel-L2 {ep:.3e} (tol {tp:.1e}) series rel-L2 {es:.3e}")
     assert ep <= tp and es <= TOL[form][1]
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
+def test_launches_beyond_the_cache():
+    """Float32 launches of more than 256 MB of work area read the next column tile
+    ahead: the same bits as launches of one block."""
+    n, hop = 1 << 22, 1 << 21
+    iq = synth.white_stream_int8(103, n + 8 * hop)  # 9 blocks of 32 MB
+    got = [gpu_run(iq, 20.0, n, 100, PERIOD, max_batch=mb) for mb in (9, 1)]
+    assert got[0][1].size == 9 * hop // 16
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
